@@ -75,6 +75,7 @@ hipError_t launch_swiglu(const aflex_ffn_args& f, void* ws, hipStream_t stream) 
   g.k_per_split = f.H;
   g.splits = 1;
   g.M = f.T;
+  g.tile_rows = tile_rows(f.T, pl.bm);
   g.max_mtiles = (f.T + pl.bm - 1) / pl.bm;
   g.n_ntiles = (f.I + gate_bn(pl.bm) - 1) / gate_bn(pl.bm);
   g.mt_major = 0;
@@ -94,6 +95,7 @@ hipError_t launch_swiglu(const aflex_ffn_args& f, void* ws, hipStream_t stream) 
   d.k_per_split = pl.down_kps;
   d.splits = pl.down_splits;
   d.M = f.T;
+  d.tile_rows = tile_rows(f.T, pl.bm);
   d.max_mtiles = (f.T + pl.bm - 1) / pl.bm;
   d.n_ntiles = (f.H + down_bn(pl.bm) - 1) / down_bn(pl.bm);
   d.mt_major = 0;
@@ -132,6 +134,7 @@ hipError_t launch_linear(const aflex_linear_args& l, void* ws, hipStream_t strea
   d.k_per_split = pl.down_kps;
   d.splits = pl.down_splits;
   d.M = l.T;
+  d.tile_rows = tile_rows(l.T, pl.bm);
   d.max_mtiles = (l.T + pl.bm - 1) / pl.bm;
   d.n_ntiles = (l.N + down_bn(pl.bm) - 1) / down_bn(pl.bm);
   d.mt_major = 0;

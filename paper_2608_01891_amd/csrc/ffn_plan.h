@@ -1,7 +1,6 @@
 // Tile and split-K planning shared by the dense and MoE FFN launchers.
 #pragma once
 #include <hip/hip_runtime.h>
-#include <math.h>
 
 #include "gemm.h"
 
@@ -23,7 +22,7 @@ inline int down_target(int bm) { return bm >= 128 ? kOneWgPerCuTarget : (bm == 6
 inline int concurrent_wgs(int bm) { return bm >= 128 ? 256 : 512; }
 
 struct FfnPlan {
-  int bm;           // rows per m-tile: 32, 64, 128 or 256
+  int bm;           // rows per m-tile: 32, 128 or 256
   int down_splits;  // split-K factor of the down GEMM
   int down_kps;     // k elements per split (multiple of 64)
 };
@@ -36,18 +35,24 @@ struct FfnPlan {
 // 128-row tile; beyond, the 256-row shape (Mixtral shapes, 128 rows per
 // expert: 828 us with 128-row tiles, 857 with 256; 160 rows: 936 and 888).
 //
-// Above 144 rows the tile is 256 or 320 rows, whichever covers an expert two
-// standard deviations above the average (routing counts spread about as a
-// binomial, sigma ~ sqrt(average)) with fewer row tiles; ties go to 256. An
-// expert just over a multiple of 256 rows would otherwise pay a nearly empty
-// tile that streams all of its weights again (Mixtral T = 2048: 472-541 rows
-// per expert, 21 row tiles of 256 against 16 of 320).
+// An expert's rows are split evenly over its row tiles (tile_rows below), so
+// one just over a multiple of 256 rows has no nearly empty tile that streams all
+// of its weights for a few rows.
 inline int pick_bm(double rows_per_expert) {
   if (rows_per_expert * 1.3 <= 32) return 32;
   if (rows_per_expert <= 48) return 64;
   if (rows_per_expert <= 144) return 128;
-  const double hi = rows_per_expert + 2.0 * sqrt(rows_per_expert);
-  return ceil(hi / 320.0) < ceil(hi / 256.0) ? 320 : 256;
+  return 256;
+}
+
+// Rows per tile when n rows take the fewest tiles of at most bm rows: even
+// shares, in whole 16-row blocks, for the 256-row tiles, whose waves multiply
+// only filled blocks and share them evenly (Mixtral T = 2048, 472-541 rows per
+// expert: three tiles of 176 rows instead of 256 + 256 + 29); else bm.
+__host__ __device__ inline int tile_rows(int n, int bm) {
+  if (bm < 256 || n <= bm) return bm;
+  const int tiles = (n + bm - 1) / bm, blocks = (n + 15) / 16;
+  return (blocks + tiles - 1) / tiles * 16;
 }
 
 // Split K of the down GEMM, keeping at least `min_steps` 64-wide k-steps per

@@ -51,6 +51,7 @@ struct GemmParams {
   int split_slots;            // > 0 (tile map only): the split count is chosen on the device from the
                               // row-tile count (at most splits) to fill rounds of split_slots work-groups
   int M;                      // dense row count (tile_map == nullptr)
+  int tile_rows;              // dense rows per m-tile (at most the kernel's tile height)
   const int32_t* tile_map;    // [max_mtiles][3] = (expert, row_begin, row_end)
   const int32_t* num_mtiles;  // device count of valid tile_map entries
   int max_mtiles;
@@ -134,6 +135,61 @@ __device__ __forceinline__ void split_plan_slots(int tiles, int ksteps, int smax
   *kps = steps * 64;
 }
 
+// The output tile of this work-group: rows [row0, row1) of the (permuted) token
+// rows, n-tile nt, k-split `split` of kps elements each. False when the
+// work-group has none (it lies beyond the device-side tile count).
+struct GemmTile {
+  int expert, row0, row1, nt, split, kps;
+};
+
+__device__ __forceinline__ bool gemm_tile_of(const GemmParams& p, GemmTile& x) {
+  int t, splits = p.splits, mrange = p.max_mtiles;
+  x.kps = p.k_per_split;
+  if (p.mt_major == 2 || p.split_slots > 0) {
+    // Row tiles from the device-side count (and the split count planned from
+    // it): the real tiles spread evenly over the XCDs. Expert-major
+    // (mt_major = 2), each XCD takes consecutive n-tiles of one or two experts,
+    // whose token rows then stay in its L2.
+    const int mtiles = *p.num_mtiles;
+    if (p.split_slots > 0) split_plan_slots(mtiles * p.n_ntiles, p.K / 64, p.splits, p.split_slots, &splits, &x.kps);
+    const int nreal = mtiles * p.n_ntiles * splits;
+    if ((int)blockIdx.x >= nreal) return false;
+    t = xcd_remap(blockIdx.x, nreal);
+    mrange = mtiles;
+  } else {
+    t = xcd_remap(blockIdx.x, gridDim.x);
+  }
+  x.split = t % splits;
+  const int rest = t / splits;
+  int mt;
+  if (p.mt_major) {
+    x.nt = rest % p.n_ntiles;
+    mt = rest / p.n_ntiles;
+  } else if (p.tile_map == nullptr && p.max_mtiles > 8) {
+    // Dense GEMMs with many row tiles: groups of 8 row tiles, row fastest, so
+    // the 32 work-groups an XCD runs at a time cover 8 A tiles x 4 weight tiles
+    // (12 tile streams through its L2 instead of 16 + 2).
+    const int per = 8 * p.n_ntiles, grp = rest / per, in = rest - grp * per;
+    const int gm = min(8, p.max_mtiles - grp * 8);
+    mt = grp * 8 + in % gm;
+    x.nt = in / gm;
+  } else {
+    mt = rest % mrange;
+    x.nt = rest / mrange;
+  }
+  x.expert = 0;
+  if (p.tile_map) {
+    if (mt >= *p.num_mtiles) return false;
+    x.expert = p.tile_map[3 * mt + 0];
+    x.row0 = p.tile_map[3 * mt + 1];
+    x.row1 = p.tile_map[3 * mt + 2];
+  } else {
+    x.row0 = mt * p.tile_rows;
+    x.row1 = min(x.row0 + p.tile_rows, p.M);
+  }
+  return true;
+}
+
 // BM x BN output tile, WM x WN waves (each a (BM/WM) x (BN/WN) sub-tile of
 // MS x MS MFMA tiles: v_mfma_f32_16x16x32_bf16 or v_mfma_f32_32x32x16_bf16),
 // BK-wide k-steps, LDS_BYTES of LDS per work-group (the ring has as many
@@ -166,52 +222,12 @@ __global__ __launch_bounds__(64 * WM * WN, LDS_BYTES > 81920 ? 1 : 2) void gemm_
   // on distinct bank groups.
   __shared__ __attribute__((aligned(16))) uint16_t sm[STAGES][ROWS * BK];
 
-  int t, splits = p.splits, kps = p.k_per_split, mrange = p.max_mtiles;
-  if (p.mt_major == 2 || p.split_slots > 0) {
-    // Row tiles from the device-side count (and the split count planned from
-    // it): the real tiles spread evenly over the XCDs. Expert-major
-    // (mt_major = 2), each XCD takes consecutive n-tiles of one or two experts,
-    // whose token rows then stay in its L2.
-    const int mtiles = *p.num_mtiles;
-    if (p.split_slots > 0) split_plan_slots(mtiles * p.n_ntiles, p.K / 64, p.splits, p.split_slots, &splits, &kps);
-    const int nreal = mtiles * p.n_ntiles * splits;
-    if ((int)blockIdx.x >= nreal) return;
-    t = xcd_remap(blockIdx.x, nreal);
-    mrange = mtiles;
-  } else {
-    t = xcd_remap(blockIdx.x, gridDim.x);
-  }
-  const int split = t % splits;
-  const int rest = t / splits;
-  int mt, nt;
-  if (p.mt_major) {
-    nt = rest % p.n_ntiles;
-    mt = rest / p.n_ntiles;
-  } else if (p.tile_map == nullptr && p.max_mtiles > 8) {
-    // Dense GEMMs with many row tiles: groups of 8 row tiles, row fastest, so
-    // the 32 work-groups an XCD runs at a time cover 8 A tiles x 4 weight tiles
-    // (12 tile streams through its L2 instead of 16 + 2).
-    const int per = 8 * p.n_ntiles, grp = rest / per, in = rest - grp * per;
-    const int gm = min(8, p.max_mtiles - grp * 8);
-    mt = grp * 8 + in % gm;
-    nt = in / gm;
-  } else {
-    mt = rest % mrange;
-    nt = rest / mrange;
-  }
-  int expert = 0, row0, row1;
-  if (p.tile_map) {
-    if (mt >= *p.num_mtiles) return;
-    expert = p.tile_map[3 * mt + 0];
-    row0 = p.tile_map[3 * mt + 1];
-    row1 = p.tile_map[3 * mt + 2];
-  } else {
-    row0 = mt * BM;
-    row1 = min(row0 + BM, p.M);
-  }
-  const int n0 = nt * BN;
-  const int kb = split * kps;
-  const int ke = min(p.K, kb + kps);
+  GemmTile x;
+  if (!gemm_tile_of(p, x)) return;
+  const int expert = x.expert, row0 = x.row0, row1 = x.row1, split = x.split;
+  const int n0 = x.nt * BN;
+  const int kb = split * x.kps;
+  const int ke = min(p.K, kb + x.kps);
   const int nk = (ke - kb) / BK;
 
   const int tid = threadIdx.x;
@@ -380,7 +396,7 @@ __global__ __launch_bounds__(64 * WM * WN, LDS_BYTES > 81920 ? 1 : 2) void gemm_
     using I3 = std::integral_constant<int, 3 <= TM ? 3 : TM>;
     using I4 = std::integral_constant<int, 4 <= TM ? 4 : TM>;
     using IT = std::integral_constant<int, TM>;
-    static_assert(TM <= 5, "row blocks per wave");
+    static_assert(TM <= 4, "row blocks per wave");
     if (nact == 1)
       kloop(I1{});
     else if (nact == 2)

@@ -140,16 +140,18 @@ __device__ __forceinline__ void stage_logits(const float* __restrict__ src, int 
   }
 }
 
-// m-tiles of bm rows per expert, in expert order (one thread).
+// m-tiles of at most bm rows per expert, in expert order (one thread).
 __device__ __forceinline__ void build_tile_map(const int* off, int E, int bm, int32_t* tile_map, int32_t* num_tiles) {
   int nt = 0;
-  for (int e = 0; e < E; ++e)
-    for (int r = off[e]; r < off[e + 1]; r += bm) {
+  for (int e = 0; e < E; ++e) {
+    const int rows = tile_rows(off[e + 1] - off[e], bm);
+    for (int r = off[e]; r < off[e + 1]; r += rows) {
       tile_map[3 * nt + 0] = e;
       tile_map[3 * nt + 1] = r;
-      tile_map[3 * nt + 2] = min(r + bm, off[e + 1]);
+      tile_map[3 * nt + 2] = min(r + rows, off[e + 1]);
       ++nt;
     }
+  }
   *num_tiles = nt;
 }
 
