@@ -575,6 +575,60 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
   }
 }
 
+// The same merge for units cut into many pieces (a few long contexts: the
+// resident work-groups per unit exceed kManyPieces): one work-group per (unit,
+// head), whose 256 / (D / 4) groups of lanes each combine a contiguous share of
+// the pieces, then the shares in order through LDS. The chain of one lane is
+// then an eighth or sixteenth of the pieces: 24 units of 32 pieces on average,
+// up to about 100 where the ranges are small, took 10.8 us in one chain.
+template <int D>
+__global__ __launch_bounds__(256) void attn_merge_many_kernel(AttnParams p) {
+  constexpr int D4 = D / 4, NG = 256 / D4;
+  __shared__ float sm_m[NG], sm_l[NG];
+  __shared__ __attribute__((aligned(16))) float sm_o[NG][D];
+  const int G = p.G;
+  const int unit = blockIdx.x / G, g = blockIdx.x - unit * G;
+  const int b = unit / p.Hkv, kvh = unit - b * p.Hkv;
+  if (clamp_ctx(p, b) == 0) return;
+  const int2 sp = p.span[unit];
+  const int wf = sp.x, wl = sp.y;
+  if (wf == wl) return;
+  const int grp = threadIdx.x / D4, d4 = threadIdx.x - grp * D4;
+  const int per = (wl - wf + NG) / NG;
+  const int w0 = wf + grp * per, w1 = min(w0 + per, wl + 1);
+  float M = kNegInf, L = 0.f;
+  f32x4 O = {0.f, 0.f, 0.f, 0.f};
+  auto join = [&](float m, float l, f32x4 o) {
+    const float Mn = fmaxf(M, m);
+    const float Mu = (Mn == kNegInf) ? 0.f : Mn;
+    const float wa = fast_exp2(M - Mu), wb = fast_exp2(m - Mu);
+    L = L * wa + l * wb;
+    O = O * wa + o * wb;
+    M = Mn;
+  };
+#pragma unroll 4
+  for (int w = w0; w < w1; ++w) {
+    const size_t s = ((size_t)unit + w) * G + g;
+    join(p.part_ml[s * 2], p.part_ml[s * 2 + 1], *reinterpret_cast<const f32x4*>(&p.part_o[s * D + d4 * 4]));
+  }
+  if (d4 == 0) {
+    sm_m[grp] = M;
+    sm_l[grp] = L;
+  }
+  *reinterpret_cast<f32x4*>(&sm_o[grp][d4 * 4]) = O;
+  __syncthreads();
+  if (grp != 0) return;
+#pragma unroll
+  for (int i = 1; i < NG; ++i) join(sm_m[i], sm_l[i], *reinterpret_cast<const f32x4*>(&sm_o[i][d4 * 4]));
+  const float inv = L > 0.f ? 1.f / L : 0.f;
+  ushort4 v;
+  v.x = f2bf(O[0] * inv);
+  v.y = f2bf(O[1] * inv);
+  v.z = f2bf(O[2] * inv);
+  v.w = f2bf(O[3] * inv);
+  *reinterpret_cast<ushort4*>(p.out + ((size_t)b * p.Hq + kvh * G + g) * D + d4 * 4) = v;
+}
+
 // ---------------------------------------------------------------------------
 // Host side.
 
@@ -602,6 +656,9 @@ static int resident_wgs() {
 // 2.71 to 2.67 ms. The layer step, whose attention stream also runs o_proj,
 // is faster with the 4-wave form (2.742 against 2.768 ms).
 constexpr int kWideWaves = 12;
+
+// Work-groups per unit from which the merge shares a unit's pieces among lanes.
+constexpr int kManyPieces = 8;
 
 static int unit_cost(const aflex_attn_args& a) { return a.split_tokens > 0 ? 0 : kUnitCost; }
 
@@ -707,7 +764,12 @@ hipError_t launch_attn_decode(const aflex_attn_args& a, void* ws, hipStream_t st
   }
   if (P > 1 && !unit) {  // with one work-group, or one per unit, no unit is split
     ProfScope ps("attn_merge", stream);
-    if (a.D == 128)
+    const bool many = P >= kManyPieces * (long long)a.B * a.Hkv;
+    if (many && a.D == 128)
+      attn_merge_many_kernel<128><<<a.B * a.Hkv * p.G, 256, 0, stream>>>(p);
+    else if (many)
+      attn_merge_many_kernel<64><<<a.B * a.Hkv * p.G, 256, 0, stream>>>(p);
+    else if (a.D == 128)
       attn_merge_kernel<128><<<a.B * a.Hkv, 256, 0, stream>>>(p);
     else
       attn_merge_kernel<64><<<a.B * a.Hkv, 256, 0, stream>>>(p);
