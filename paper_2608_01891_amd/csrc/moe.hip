@@ -9,8 +9,8 @@
 //      prefix, the stable (expert, token, slot) order of the token/slot pairs,
 //      each pair's position in that order, and the m-tile map of the grouped
 //      GEMMs. One work-group up to 512 tokens, else three kernels over chunks
-//      of 256 tokens; ranks come from wave ballots, so the order is
-//      deterministic (and the same for both paths).
+//      of 256 tokens; ranks count the expert's earlier tokens (bit masks, wave
+//      ballots), so the order is deterministic (and the same for both paths).
 //   2. grouped gate/up GEMM with fused SwiGLU; the A rows are gathered from x
 //      through the pair order (no permuted copy of x is written).
 //   3. grouped down GEMM into fp32 split-K partials, rows in pair order.
@@ -119,19 +119,20 @@ __device__ __forceinline__ void topk_token(const float* l, int E, int k, int* si
 // top-k then reads LDS instead of issuing one dependent global load per
 // compared logit (about 16 serial memory round trips per token at E = 8,
 // k = 2).
+template <int NT>
 __device__ __forceinline__ void stage_logits(const float* __restrict__ src, int rows, int E, int ls, float* s_log,
                                              int tid) {
   const int n = rows * E;
-  for (int i0 = 0; i0 < n; i0 += 256 * 8) {
+  for (int i0 = 0; i0 < n; i0 += NT * 8) {
     float v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int i = i0 + u * 256 + tid;
+      const int i = i0 + u * NT + tid;
       v[u] = i < n ? src[i] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int i = i0 + u * 256 + tid;
+      const int i = i0 + u * NT + tid;
       if (i < n) {
         const int r = i / E;
         s_log[r * ls + (i - r * E)] = v[u];
@@ -140,19 +141,103 @@ __device__ __forceinline__ void stage_logits(const float* __restrict__ src, int 
   }
 }
 
-// m-tiles of at most bm rows per expert, in expert order (one thread).
-__device__ __forceinline__ void build_tile_map(const int* off, int E, int bm, int32_t* tile_map, int32_t* num_tiles) {
-  int nt = 0;
-  for (int e = 0; e < E; ++e) {
-    const int rows = tile_rows(off[e + 1] - off[e], bm);
-    for (int r = off[e]; r < off[e + 1]; r += rows) {
-      tile_map[3 * nt + 0] = e;
-      tile_map[3 * nt + 1] = r;
-      tile_map[3 * nt + 2] = min(r + rows, off[e + 1]);
-      ++nt;
+// Top-k of one token by the 8 lanes of its group (lane j of the group holds
+// logits [8 j, 8 j + 8), E <= 64), the same choice as topk_token: the largest
+// untaken logit, ties to the lower id (a NaN is only taken as the first untaken
+// one). Lane j < k returns slot j's expert and weight. For many experts: with
+// one thread per token the 8 x 64 dependent compares and LDS reads of E = 64,
+// k = 8 made the whole routing of 24 tokens take 108 us; one round here is a
+// tournament over 8 registers and three DPP exchanges.
+__device__ __forceinline__ void topk_lanes(const float* __restrict__ row, bool valid, int E, int k, int j8, int lane,
+                                           int* id_out, float* w_out) {
+  float l[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) l[i] = (valid && j8 * 8 + i < E) ? row[j8 * 8 + i] : 0.f;
+  const uint64_t all = E == 64 ? ~0ull : (1ull << E) - 1ull;
+  uint64_t taken = ~all;
+  int my_id = 0;
+  float my_v = 0.f, v0 = 0.f;
+  for (int s = 0; s < k; ++s) {
+    float bv = kNegInf;
+    int bi = 127;  // loses every tie
+#pragma unroll
+    for (int i = 7; i >= 0; --i) {  // (descending, so >= leaves ties to the lower id)
+      const int e = j8 * 8 + i;
+      const bool ok = !((taken >> e) & 1) && l[i] >= bv;
+      bv = ok ? l[i] : bv;
+      bi = ok ? e : bi;
+    }
+    const int f = __builtin_ctzll(~taken);
+    if ((f >> 3) == j8) {
+      float lf = l[0];
+#pragma unroll
+      for (int i = 1; i < 8; ++i) lf = (f & 7) == i ? l[i] : lf;
+      if (lf != lf) {
+        bv = -kNegInf;
+        bi = f - 64;  // wins every tie
+      }
+    }
+    auto meet = [&](float ov, int oi) {
+      const bool t = ov > bv || (ov == bv && oi < bi);
+      bv = t ? ov : bv;
+      bi = t ? oi : bi;
+    };
+#define AFLEX_DPP(X, CTRL) __builtin_amdgcn_update_dpp(X, X, CTRL, 0xf, 0xf, false)
+    meet(__int_as_float(AFLEX_DPP(__float_as_int(bv), 0xB1)), AFLEX_DPP(bi, 0xB1));    // lane ^ 1
+    meet(__int_as_float(AFLEX_DPP(__float_as_int(bv), 0x4E)), AFLEX_DPP(bi, 0x4E));    // lane ^ 2
+    meet(__int_as_float(AFLEX_DPP(__float_as_int(bv), 0x141)), AFLEX_DPP(bi, 0x141));  // the group's other four
+#undef AFLEX_DPP
+    if (bi < 0) {
+      bi += 64;
+      bv = __builtin_nanf("");
+    }
+    taken |= 1ull << bi;
+    v0 = s == 0 ? bv : v0;
+    if (s == j8) {
+      my_id = bi;
+      my_v = bv;
     }
   }
-  *num_tiles = nt;
+  const float ex = j8 < k ? expf(my_v - v0) : 0.f;
+  float z = 0.f;
+  for (int s = 0; s < k; ++s) z += __shfl(ex, (lane & ~7) + s);
+  *id_out = my_id;
+  *w_out = ex / z;
+}
+
+// Exclusive offsets of the experts' pair counts and the m-tile map (at most bm
+// rows per tile, in expert order) by one wave, lane e for expert e: cnt is the
+// lane's count (0 past E).
+__device__ __forceinline__ void plan_tiles(int cnt, int lane, int E, int bm, int* off, int32_t* offsets,
+                                           int32_t* u_offsets, int32_t* tile_map, int32_t* num_tiles) {
+  const int rows = tile_rows(cnt, bm), n = (cnt + rows - 1) / rows;
+  int incl = cnt, tincl = n;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int a = __shfl_up(incl, o), t = __shfl_up(tincl, o);
+    if (lane >= o) {
+      incl += a;
+      tincl += t;
+    }
+  }
+  const int first = incl - cnt, nt = tincl - n;
+  off[lane] = first;  // (off[E] is the total: lanes past E count nothing)
+  if (lane == 63) off[64] = incl;
+  if (lane < E) {
+    offsets[lane] = first;
+    if (u_offsets) u_offsets[lane] = first;
+    if (lane == E - 1) {
+      offsets[E] = incl;
+      if (u_offsets) u_offsets[E] = incl;
+      *num_tiles = tincl;
+    }
+    for (int i = 0; i < n; ++i) {
+      int32_t* m = tile_map + 3 * (nt + i);
+      m[0] = lane;
+      m[1] = first + i * rows;
+      m[2] = first + min((i + 1) * rows, cnt);
+    }
+  }
 }
 
 // Stable rank of each of a 256-token chunk's pairs among the chunk's pairs of
@@ -178,81 +263,91 @@ __device__ __forceinline__ void chunk_ranks(const int* my_e, bool valid, int E, 
   }
 }
 
-__global__ __launch_bounds__(256) void moe_route_kernel(const float* __restrict__ logits, int T, int E, int k,
+// Experts above which a token's top-k is shared by 8 lanes (topk_lanes): up to
+// 16 experts one thread per token has few compares and no exchanges.
+constexpr int kThreadTopkMaxE = 16;
+
+// The whole routing of up to kSingleRouteMaxT tokens in one work-group. What
+// bounds it is the chain of dependent steps, so each is done by as many lanes as
+// it has items: the top-k, then per expert a bit mask of its tokens in LDS; one
+// wave scans the experts' counts for the offsets and the tile map; a pair's
+// stable rank is the number of its expert's mask bits below its token.
+// (One thread building offsets and map, and ranks by ballots over all experts:
+// E = 64, k = 8, 24 tokens 108 us in all, E = 8, k = 2, 256 tokens 12.)
+__global__ __launch_bounds__(512) void moe_route_kernel(const float* __restrict__ logits, int T, int E, int k,
                                                         int bm, int32_t* ids, float* wts, int32_t* offsets,
                                                         int32_t* sorted, int32_t* pos, int32_t* tile_map,
                                                         int32_t* num_tiles, int32_t* u_ids, float* u_w,
                                                         int32_t* u_offsets, int32_t* u_sorted) {
-  __shared__ int cnt[kMaxE];
+  constexpr int kWords = kSingleRouteMaxT / 32;
+  static_assert(kSingleRouteMaxT == 512, "one thread per token");
   __shared__ int off[kMaxE + 1];
-  __shared__ int base[kMaxE];
-  __shared__ int wcnt[4][kMaxE];
-  __shared__ float s_log[256 * (kMaxE + 1)];        // one chunk's logits, rows of odd stride
-  __shared__ int s_ids[kSingleRouteMaxT * kMaxK];  // selected experts, read back by step 3
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int ls = E | 1;
-  if (tid < kMaxE) {
-    cnt[tid] = 0;
-    base[tid] = 0;
-  }
-  __syncthreads();
+  __shared__ uint32_t mask[kMaxE * (kWords + 1)];             // tokens of each expert, rows of odd stride
+  __shared__ float s_log[512 * (kThreadTopkMaxE + 1)];        // logits, rows of odd stride
+  __shared__ uint8_t s_ids[kSingleRouteMaxT * kMaxK];         // selected experts, read back for the ranks
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int nw = (T + 31) >> 5;
+  for (int i = tid; i < E * (kWords + 1); i += 512) mask[i] = 0;
 
-  // 1. top-k and softmax over the selected logits, 256 tokens at a time.
-  for (int c0 = 0; c0 < T; c0 += 256) {
-    stage_logits(logits + (size_t)c0 * E, min(256, T - c0), E, ls, s_log, tid);
+  // 1. top-k and softmax over the selected logits.
+  if (E <= kThreadTopkMaxE) {
+    const int ls = E | 1;
+    stage_logits<512>(logits, T, E, ls, s_log, tid);
     __syncthreads();
-    const int t = c0 + tid;
-    if (t < T) {
+    if (tid < T) {
       int sid[kMaxK];
       float w[kMaxK];
       topk_token(s_log + tid * ls, E, k, sid, w);
       for (int j = 0; j < k; ++j) {
-        ids[t * k + j] = sid[j];
-        wts[t * k + j] = w[j];
-        s_ids[t * k + j] = sid[j];
-        if (u_ids) u_ids[t * k + j] = sid[j];
-        if (u_w) u_w[t * k + j] = w[j];
-        atomicAdd(&cnt[sid[j]], 1);
+        const int e = sid[j], i = tid * k + j;
+        ids[i] = e;
+        wts[i] = w[j];
+        s_ids[i] = static_cast<uint8_t>(e);
+        if (u_ids) u_ids[i] = e;
+        if (u_w) u_w[i] = w[j];
+        atomicOr(&mask[e * (kWords + 1) + (tid >> 5)], 1u << (tid & 31));
       }
     }
+  } else {
     __syncthreads();
-  }
-
-  // 2. offsets and the m-tile map.
-  if (tid == 0) {
-    off[0] = 0;
-    for (int e = 0; e < E; ++e) off[e + 1] = off[e] + cnt[e];
-    build_tile_map(off, E, bm, tile_map, num_tiles);
+    for (int t0 = 0; t0 < T; t0 += 64) {
+      const int t = t0 + (tid >> 3), j = tid & 7;
+      int e;
+      float w;
+      topk_lanes(logits + (size_t)t * E, t < T, E, k, j, lane, &e, &w);
+      if (t < T && j < k) {
+        const int i = t * k + j;
+        ids[i] = e;
+        wts[i] = w;
+        s_ids[i] = static_cast<uint8_t>(e);
+        if (u_ids) u_ids[i] = e;
+        if (u_w) u_w[i] = w;
+        atomicOr(&mask[e * (kWords + 1) + (t >> 5)], 1u << (t & 31));
+      }
+    }
   }
   __syncthreads();
-  if (tid <= E) {
-    offsets[tid] = off[tid];
-    if (u_offsets) u_offsets[tid] = off[tid];
+
+  // 2. offsets and the m-tile map.
+  if (tid < 64) {
+    int cnt = 0;
+    if (lane < E)
+      for (int w = 0; w < nw; ++w) cnt += __popc(mask[lane * (kWords + 1) + w]);
+    plan_tiles(cnt, lane, E, bm, off, offsets, u_offsets, tile_map, num_tiles);
   }
+  __syncthreads();
 
   // 3. stable ranks: pairs of expert e are ordered by token (a token holds e
-  //    at most once), chunk by chunk of 256 tokens, wave by wave, lane by lane.
-  for (int c0 = 0; c0 < T; c0 += 256) {
-    const int t = c0 + tid;
-    const bool valid = t < T;
-    int my_e[kMaxK], pre[kMaxK];
-    for (int j = 0; j < k; ++j) my_e[j] = valid ? s_ids[t * k + j] : -1;
-    chunk_ranks(my_e, valid, E, k, wave, lane, pre, wcnt);
-    __syncthreads();
-    if (valid) {
-      for (int j = 0; j < k; ++j) {
-        const int e = my_e[j];
-        int r = base[e] + pre[j];
-        for (int w = 0; w < wave; ++w) r += wcnt[w][e];
-        const int pidx = off[e] + r;
-        sorted[pidx] = t * k + j;
-        pos[t * k + j] = pidx;
-        if (u_sorted) u_sorted[pidx] = t * k + j;
-      }
-    }
-    __syncthreads();
-    if (tid < E) base[tid] += wcnt[0][tid] + wcnt[1][tid] + wcnt[2][tid] + wcnt[3][tid];
-    __syncthreads();
+  //    at most once).
+  for (int i = tid; i < T * k; i += 512) {
+    const int e = s_ids[i], t = i / k;
+    const uint32_t* m = mask + e * (kWords + 1);
+    int rank = __popc(m[t >> 5] & ((1u << (t & 31)) - 1u));
+    for (int w = 0; w < (t >> 5); ++w) rank += __popc(m[w]);
+    const int pidx = off[e] + rank;
+    sorted[pidx] = i;
+    pos[i] = pidx;
+    if (u_sorted) u_sorted[pidx] = i;
   }
 }
 
@@ -265,56 +360,61 @@ __global__ __launch_bounds__(256) void moe_topk_kernel(const float* __restrict__
                                                        int32_t* ids, float* wts, int32_t* u_ids, float* u_w,
                                                        int32_t* blockcnt) {
   __shared__ int cnt[kMaxE];
-  __shared__ float s_log[256 * (kMaxE + 1)];
+  __shared__ float s_log[256 * (kThreadTopkMaxE + 1)];
   const int tid = threadIdx.x;
-  const int ls = E | 1;
   if (tid < kMaxE) cnt[tid] = 0;
   const int t0 = blockIdx.x * 256;
-  stage_logits(logits + (size_t)t0 * E, min(256, T - t0), E, ls, s_log, tid);
-  __syncthreads();
-  const int t = t0 + tid;
-  if (t < T) {
-    int sid[kMaxK];
-    float w[kMaxK];
-    topk_token(s_log + tid * ls, E, k, sid, w);
-    for (int j = 0; j < k; ++j) {
-      ids[t * k + j] = sid[j];
-      wts[t * k + j] = w[j];
-      if (u_ids) u_ids[t * k + j] = sid[j];
-      if (u_w) u_w[t * k + j] = w[j];
-      atomicAdd(&cnt[sid[j]], 1);
+  if (E <= kThreadTopkMaxE) {
+    const int ls = E | 1;
+    stage_logits<256>(logits + (size_t)t0 * E, min(256, T - t0), E, ls, s_log, tid);
+    __syncthreads();
+    const int t = t0 + tid;
+    if (t < T) {
+      int sid[kMaxK];
+      float w[kMaxK];
+      topk_token(s_log + tid * ls, E, k, sid, w);
+      for (int j = 0; j < k; ++j) {
+        ids[t * k + j] = sid[j];
+        wts[t * k + j] = w[j];
+        if (u_ids) u_ids[t * k + j] = sid[j];
+        if (u_w) u_w[t * k + j] = w[j];
+        atomicAdd(&cnt[sid[j]], 1);
+      }
+    }
+  } else {
+    __syncthreads();
+    for (int c = 0; c < 256 && t0 + c < T; c += 32) {
+      const int t = t0 + c + (tid >> 3), j = tid & 7;
+      int e;
+      float w;
+      topk_lanes(logits + (size_t)t * E, t < T, E, k, j, tid & 63, &e, &w);
+      if (t < T && j < k) {
+        ids[t * k + j] = e;
+        wts[t * k + j] = w;
+        if (u_ids) u_ids[t * k + j] = e;
+        if (u_w) u_w[t * k + j] = w;
+        atomicAdd(&cnt[e], 1);
+      }
     }
   }
   __syncthreads();
   if (tid < E) blockcnt[(size_t)blockIdx.x * E + tid] = cnt[tid];
 }
 
-__global__ __launch_bounds__(256) void moe_offsets_kernel(const int32_t* __restrict__ blockcnt, int nblk, int E,
+__global__ __launch_bounds__(64) void moe_offsets_kernel(const int32_t* __restrict__ blockcnt, int nblk, int E,
                                                           int bm, int32_t* offsets, int32_t* u_offsets,
                                                           int32_t* tile_map, int32_t* num_tiles,
                                                           int32_t* blockbase) {
-  __shared__ int tot[kMaxE];
   __shared__ int off[kMaxE + 1];
-  const int tid = threadIdx.x;
-  if (tid < E) {
-    int sum = 0;
+  const int lane = threadIdx.x;
+  int sum = 0;
+  if (lane < E) {
     for (int b = 0; b < nblk; ++b) {
-      blockbase[(size_t)b * E + tid] = sum;
-      sum += blockcnt[(size_t)b * E + tid];
+      blockbase[(size_t)b * E + lane] = sum;
+      sum += blockcnt[(size_t)b * E + lane];
     }
-    tot[tid] = sum;
   }
-  __syncthreads();
-  if (tid == 0) {
-    off[0] = 0;
-    for (int e = 0; e < E; ++e) off[e + 1] = off[e] + tot[e];
-    build_tile_map(off, E, bm, tile_map, num_tiles);
-  }
-  __syncthreads();
-  if (tid <= E) {
-    offsets[tid] = off[tid];
-    if (u_offsets) u_offsets[tid] = off[tid];
-  }
+  plan_tiles(sum, lane, E, bm, off, offsets, u_offsets, tile_map, num_tiles);
 }
 
 __global__ __launch_bounds__(256) void moe_rank_kernel(const int32_t* __restrict__ ids, int T, int E, int k,
@@ -429,7 +529,7 @@ hipError_t launch_moe_route(const aflex_ffn_args& f, void* route_ws, hipStream_t
   int32_t* num_tiles = reinterpret_cast<int32_t*>(w + L.num_tiles);
   ProfScope ps("moe_route", stream);
   if (f.T <= kSingleRouteMaxT) {
-    moe_route_kernel<<<1, 256, 0, stream>>>(f.router_logits, f.T, f.E, f.k, L.bm, ids, wts, offsets, sorted, pos,
+    moe_route_kernel<<<1, 512, 0, stream>>>(f.router_logits, f.T, f.E, f.k, L.bm, ids, wts, offsets, sorted, pos,
                                             tile_map, num_tiles, f.topk_ids, f.topk_w, f.expert_offsets,
                                             f.sorted_pairs);
     return hipGetLastError();
@@ -439,7 +539,7 @@ hipError_t launch_moe_route(const aflex_ffn_args& f, void* route_ws, hipStream_t
   int32_t* blockbase = reinterpret_cast<int32_t*>(w + L.blockbase);
   moe_topk_kernel<<<nblk, 256, 0, stream>>>(f.router_logits, f.T, f.E, f.k, ids, wts, f.topk_ids, f.topk_w,
                                             blockcnt);
-  moe_offsets_kernel<<<1, 256, 0, stream>>>(blockcnt, nblk, f.E, L.bm, offsets, f.expert_offsets, tile_map,
+  moe_offsets_kernel<<<1, 64, 0, stream>>>(blockcnt, nblk, f.E, L.bm, offsets, f.expert_offsets, tile_map,
                                             num_tiles, blockbase);
   moe_rank_kernel<<<nblk, 256, 0, stream>>>(ids, f.T, f.E, f.k, offsets, blockbase, sorted, pos,
                                             f.sorted_pairs);

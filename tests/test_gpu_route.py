@@ -1,0 +1,35 @@
+"""MoE routing: the chosen experts, weights, offsets and pair order, exactly, at
+the edges of its three paths (one thread or eight lanes per token, one
+work-group up to 512 tokens), with ties, infinities and skewed loads."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2608_01891_amd import aflex, synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("E,k", [(8, 2), (16, 8), (17, 1), (33, 8), (63, 4), (64, 8)])
+@pytest.mark.parametrize("T", [1, 33, 64, 65, 512, 513])
+def test_routing_exact(gpu_lib, T, E, k):
+    rng = np.random.default_rng([T, E, k])
+    logits = np.round(rng.standard_normal((T, E)).astype(np.float32) * 2) / 2  # many ties
+    logits[rng.random((T, E)) < 0.05] = -np.inf
+    logits[:, E - 1] += (np.arange(T) % 3 == 0) * np.float32(9)  # a crowded last expert
+    logits[T // 2] = 0.0  # a token without any order
+    logits[T // 3, :] = -1e30
+    logits = torch.from_numpy(logits)
+    x, w, _ = synth.custom_ffn(41, T, 64, 64, E=E)
+    _, r = aflex.moe_ffn(x.to(DEV), w.to(DEV), logits.to(DEV), k, routing=True)
+    ids, wts = oracle.route_topk(logits, k)
+    assert torch.equal(r["topk_ids"].cpu().long(), ids)
+    # expf and one division in fp32: a few units in the last place
+    assert torch.allclose(r["topk_w"].cpu().double(), wts.double(), rtol=1e-5, atol=1e-7)
+    flat = ids.reshape(-1).numpy()
+    order = np.lexsort((np.arange(flat.size), flat))  # by expert, then token and slot
+    assert np.array_equal(r["sorted_pairs"].cpu().numpy(), order)
+    counts = np.bincount(flat, minlength=E)
+    assert np.array_equal(r["expert_offsets"].cpu().numpy(), np.concatenate([[0], np.cumsum(counts)]))
