@@ -17,7 +17,7 @@
 //
 // Rows: 16-row block 2 i + wm of the tile is block i of the waves with row index
 // wm, so a partly filled tile is shared evenly by the waves; only filled blocks
-// are multiplied (in instances of 8, 6, 4 or 2 blocks per wave).
+// are loaded and multiplied (in instances of 8, 6, 4 or 2 blocks per wave).
 //
 // Measured (dense SwiGLU, H = 5120, I = 25600; the eight-wave 32x32x16 tiles
 // with two 64-wide stages before): T = 4096 2870 -> 2350 us (1.12 -> 1.37
@@ -44,8 +44,12 @@ __device__ __forceinline__ void unroll_for(F&& f) {
 // Direct HBM -> LDS loads of 16 bytes per lane as lds_dma16, without restoring
 // m0 (nothing else in the kernel that uses them reads it); the first takes a
 // uniform base and a per-lane byte offset.
+template <bool NT>
 __device__ __forceinline__ void lds_dma16_s(const void* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(voff), "s"(lds) : "memory");
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %1, %0 nt" ::"s"(base), "v"(voff), "s"(lds) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(voff), "s"(lds) : "memory");
 }
 __device__ __forceinline__ void lds_dma16_v(const void* gptr, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds) : "memory");
@@ -58,7 +62,7 @@ __device__ __forceinline__ void mfma_acc(f32x4& acc, bf16x8 b, bf16x8 a) {
 
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8); }
 
-template <bool DUAL, bool OUT_F32>
+template <bool DUAL, bool OUT_F32, bool NT_B = false>
 __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
   constexpr int BN = DUAL ? 128 : 256;
   constexpr int HB = 128 * 64 * 2;  // bytes of a half tile: 128 rows x 64 k
@@ -118,10 +122,12 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
   do {                                                          \
     const uint32_t d_ = wlds + (SLOT) + (J) * 4096;              \
     if constexpr ((Q) == 0 || (Q) == 3) {                        \
-      lds_dma16_v(asrc[(Q) / 3][J], d_);                         \
-      asrc[(Q) / 3][J] += step;                                  \
+      if constexpr (((Q) / 3 * 4 + (J)) < N) {                   \
+        lds_dma16_v(asrc[(Q) / 3][J], d_);                       \
+        asrc[(Q) / 3][J] += step;                                \
+      }                                                         \
     } else {                                                    \
-      lds_dma16_s(bsrc[((Q) - 1) & 1][J], bvoff, d_);            \
+      lds_dma16_s<NT_B>(bsrc[((Q) - 1) & 1][J], bvoff, d_);            \
       bsrc[((Q) - 1) & 1][J] += step;                            \
     }                                                           \
   } while (0)
@@ -139,7 +145,10 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
   const uint32_t boff[2] = {offb + wn * 8192, (offb ^ 64) + wn * 8192};
 
   auto kloop = [&](auto cn) {
-    constexpr int N = decltype(cn)::value;  // row blocks of this wave that are multiplied
+    // Row blocks of each wave that are multiplied: N, 32 N rows of the tile, the
+    // same for all waves; wave-loads of A rows past them are left out, so a
+    // k-step takes 8 + N wave-loads, its first two half tiles 4 + min(N, 4).
+    constexpr int N = decltype(cn)::value;
     bf16x8 fa[2][8], fb[2][8];
     // Fragment X of k-chunk C: X < 8 weight block X, else row block X - 8. U is
     // the ring offset of the k-step's first two half tiles, V of the other two.
@@ -163,12 +172,12 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
         RING_ISSUE(Q, (decltype(s)::value * 4 + Q) * HB, L & 3);
       });
     });
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(16));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(8 + N));
     __syncthreads();
     // Ring offsets: (u, v) of this k-step, vp = v of the one before (where the
     // third k-step's first half tiles go), (un, vn) of the next.
     int u = 0, v = 2 * HB, vp = 8 * HB, un = 4 * HB, vn = 6 * HB;
-    if constexpr (N > 0) unroll_for<8 + N>([&](auto f) { RING_READ(0, decltype(f)::value, 0, 2 * HB); });
+    unroll_for<8 + N>([&](auto f) { RING_READ(0, decltype(f)::value, 0, 2 * HB); });
     for (int kt = 0; kt < nk; ++kt) {
       load_step();
       // 16 slots (2 k-chunks of 32 x 8): a slot multiplies one row block, reads
@@ -179,8 +188,8 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
         constexpr int S = decltype(ss)::value, C = S >> 3, I = S & 7, Q = S >> 2;
         if constexpr (S == 8) {
           // Every fragment of k-step kt is in registers and k-step kt + 1 has
-          // landed (the 8 wave-loads since may be in flight), for all waves.
-          __builtin_amdgcn_s_waitcnt(vmcnt_imm(8));
+          // landed (the wave-loads since may be in flight), for all waves.
+          __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 + (N < 4 ? N : 4)));
           __syncthreads();
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -192,7 +201,7 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
             mfma_acc(acc[I][2 * G], fb[C][2 * G], fa[C][I]);
             mfma_acc(acc[I][2 * G + 1], fb[C][2 * G + 1], fa[C][I]);
           }
-          if constexpr (G < XN && X < 8 + N && N > 0) {
+          if constexpr (G < XN && X < 8 + N) {
             if constexpr (C == 0)
               RING_READ(1, X, u, v);
             else
@@ -218,19 +227,16 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
       asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]), "+a"(acc[i][4]),
                         "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7]));
   };
-  const int nblk = (x.row1 - x.row0 + 15) >> 4;
-  const int nact = min(max((nblk - wm + 1) >> 1, 0), 8);
+  const int rows = x.row1 - x.row0;
   if (nk > 0) {
-    if (nact > 6)
+    if (rows > 192)
       kloop(std::integral_constant<int, 8>{});
-    else if (nact > 4)
+    else if (rows > 128)
       kloop(std::integral_constant<int, 6>{});
-    else if (nact > 2)
+    else if (rows > 64)
       kloop(std::integral_constant<int, 4>{});
-    else if (nact > 0)
-      kloop(std::integral_constant<int, 2>{});
     else
-      kloop(std::integral_constant<int, 0>{});
+      kloop(std::integral_constant<int, 2>{});
   }
 #undef RING_ISSUE
 #undef RING_READ
