@@ -74,13 +74,16 @@ __device__ __forceinline__ uint32_t lds_offset(const void* p) {
 // Direct HBM -> LDS load of 16 bytes per lane: lane l writes LDS bytes
 // [lds + 16 l, lds + 16 l + 16). Issued as inline assembly so the compiler's
 // wait-count pass does not serialise it against reads of other LDS stages;
-// callers order it with explicit s_waitcnt vmcnt and barriers.
+// callers order it with explicit s_waitcnt vmcnt and barriers. The load reads m0
+// one wait state after it is written at the earliest (the compiler does not
+// insert it within a statement).
 __device__ __forceinline__ void lds_dma16(const void* gptr, uint32_t lds) {
   const uint32_t lds_s = __builtin_amdgcn_readfirstlane(lds);  // uniform across the wave
   uint32_t saved;  // m0 is reserved to the compiler: restore it after the load
   asm volatile(
       "s_mov_b32 %0, m0\n\t"
       "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
       "global_load_lds_dwordx4 %1, off\n\t"
       "s_mov_b32 m0, %0"
       : "=&s"(saved)
@@ -97,6 +100,7 @@ __device__ __forceinline__ void lds_dma16_nt(const void* gptr, uint32_t lds) {
   asm volatile(
       "s_mov_b32 %0, m0\n\t"
       "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
       "global_load_lds_dwordx4 %1, off nt\n\t"
       "s_mov_b32 m0, %0"
       : "=&s"(saved)

@@ -47,12 +47,12 @@ __device__ __forceinline__ void unroll_for(F&& f) {
 template <bool NT>
 __device__ __forceinline__ void lds_dma16_s(const void* base, uint32_t voff, uint32_t lds) {
   if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %1, %0 nt" ::"s"(base), "v"(voff), "s"(lds) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0 nt" ::"s"(base), "v"(voff), "s"(lds) : "memory");
   else
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(voff), "s"(lds) : "memory");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" ::"s"(base), "v"(voff), "s"(lds) : "memory");
 }
 __device__ __forceinline__ void lds_dma16_v(const void* gptr, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds) : "memory");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds) : "memory");
 }
 
 // acc += b . a on the matrix cores, the accumulator held in AGPRs.
