@@ -8,9 +8,9 @@
 //      softmax over the k selected logits; per-expert counts, their exclusive
 //      prefix, the stable (expert, token, slot) order of the token/slot pairs,
 //      each pair's position in that order, and the m-tile map of the grouped
-//      GEMMs. One work-group up to 512 tokens, else three kernels over chunks
-//      of 256 tokens; ranks count the expert's earlier tokens (bit masks, wave
-//      ballots), so the order is deterministic (and the same for both paths).
+//      GEMMs. One work-group up to 512 tokens, else two kernels over chunks of
+//      64 tokens; ranks count the expert's earlier tokens in bit masks, so the
+//      order is deterministic (and the same for both paths).
 //   2. grouped gate/up GEMM with fused SwiGLU; the A rows are gathered from x
 //      through the pair order (no permuted copy of x is written).
 //   3. grouped down GEMM into fp32 split-K partials, rows in pair order.
@@ -26,14 +26,15 @@ namespace aflex {
 constexpr int kMaxK = 8;
 constexpr int kMaxE = 64;
 // Up to this many tokens one work-group routes the batch (a single launch);
-// larger batches take three kernels that spread the tokens over work-groups.
+// larger batches take two kernels over chunks of kChunk tokens.
 constexpr int kSingleRouteMaxT = 512;
+constexpr int kChunk = 64;
 
 // Workspace: a routing block (ids .. num_tiles, written by the route kernel)
 // followed by the expert block (h, P). The two can live apart: the pipeline
 // keeps one routing block per microbatch and one shared expert block.
 struct MoeLayout {
-  size_t ids, wts, offsets, sorted, pos, tile_map, num_tiles, blockcnt, blockbase, route_total;
+  size_t ids, wts, offsets, sorted, pos, tile_map, num_tiles, blockcnt, route_total;
   size_t h, P, expert_total;
   int bm, max_tiles, down_splits, down_kps;
   // 64- and 128-row tiles: experts' rows are expected to fit one tile
@@ -68,9 +69,7 @@ static MoeLayout moe_layout(const aflex_ffn_args& f) {
   L.pos = take(pairs * 4);
   L.tile_map = take((size_t)L.max_tiles * 3 * 4);
   L.num_tiles = take(4);
-  const size_t nblk = ((size_t)f.T + 255) / 256;
-  L.blockcnt = take(nblk * f.E * 4);
-  L.blockbase = take(nblk * f.E * 4);
+  L.blockcnt = take(((size_t)f.T + kChunk - 1) / kChunk * f.E * 4);
   L.route_total = o;
   o = 0;
   L.h = take(pairs * f.I * 2);
@@ -207,8 +206,8 @@ __device__ __forceinline__ void topk_lanes(const float* __restrict__ row, bool v
 
 // Exclusive offsets of the experts' pair counts and the m-tile map (at most bm
 // rows per tile, in expert order) by one wave, lane e for expert e: cnt is the
-// lane's count (0 past E).
-__device__ __forceinline__ void plan_tiles(int cnt, int lane, int E, int bm, int* off, int32_t* offsets,
+// lane's count (0 past E). Offsets go to `off`, and with `publish` to memory, where the map goes.
+__device__ __forceinline__ void plan_tiles(int cnt, int lane, int E, int bm, bool publish, int* off, int32_t* offsets,
                                            int32_t* u_offsets, int32_t* tile_map, int32_t* num_tiles) {
   const int rows = tile_rows(cnt, bm), n = (cnt + rows - 1) / rows;
   int incl = cnt, tincl = n;
@@ -223,7 +222,7 @@ __device__ __forceinline__ void plan_tiles(int cnt, int lane, int E, int bm, int
   const int first = incl - cnt, nt = tincl - n;
   off[lane] = first;  // (off[E] is the total: lanes past E count nothing)
   if (lane == 63) off[64] = incl;
-  if (lane < E) {
+  if (publish && lane < E) {
     offsets[lane] = first;
     if (u_offsets) u_offsets[lane] = first;
     if (lane == E - 1) {
@@ -237,29 +236,6 @@ __device__ __forceinline__ void plan_tiles(int cnt, int lane, int E, int bm, int
       m[1] = first + i * rows;
       m[2] = first + min((i + 1) * rows, cnt);
     }
-  }
-}
-
-// Stable rank of each of a 256-token chunk's pairs among the chunk's pairs of
-// the same expert (token order, i.e. wave by wave, lane by lane): pre[j] within
-// the wave, wcnt[w][e] the pairs of expert e in wave w.
-__device__ __forceinline__ void chunk_ranks(const int* my_e, bool valid, int E, int k, int wave, int lane, int* pre,
-                                            int (*wcnt)[kMaxE]) {
-  const uint64_t lt = (1ull << lane) - 1ull;
-  uint64_t mask = 0;
-  for (int j = 0; j < k; ++j) {
-    pre[j] = 0;
-    if (valid) mask |= 1ull << my_e[j];
-  }
-  for (int e = 0; e < E; ++e) {
-    const bool f = (mask >> e) & 1ull;
-    const uint64_t bal = __ballot(f);
-    if (f) {
-      const int pr = __popcll(bal & lt);
-      for (int j = 0; j < k; ++j)
-        if (my_e[j] == e) pre[j] = pr;
-    }
-    if (lane == 0) wcnt[wave][e] = __popcll(bal);
   }
 }
 
@@ -333,7 +309,7 @@ __global__ __launch_bounds__(512) void moe_route_kernel(const float* __restrict_
     int cnt = 0;
     if (lane < E)
       for (int w = 0; w < nw; ++w) cnt += __popc(mask[lane * (kWords + 1) + w]);
-    plan_tiles(cnt, lane, E, bm, off, offsets, u_offsets, tile_map, num_tiles);
+    plan_tiles(cnt, lane, E, bm, true, off, offsets, u_offsets, tile_map, num_tiles);
   }
   __syncthreads();
 
@@ -351,94 +327,108 @@ __global__ __launch_bounds__(512) void moe_route_kernel(const float* __restrict_
   }
 }
 
-// The same routing for larger batches in three kernels, so that the per-token
-// work is spread over one work-group per 256 tokens instead of looping in one:
-// (1) top-k and the chunk's expert counts, (2) offsets, tile map and each
-// chunk's first rank per expert, (3) the chunk's stable ranks. The pair order
-// is the single kernel's.
-__global__ __launch_bounds__(256) void moe_topk_kernel(const float* __restrict__ logits, int T, int E, int k,
-                                                       int32_t* ids, float* wts, int32_t* u_ids, float* u_w,
-                                                       int32_t* blockcnt) {
-  __shared__ int cnt[kMaxE];
-  __shared__ float s_log[256 * (kThreadTopkMaxE + 1)];
+// Batches of more than kSingleRouteMaxT tokens, in two launches over chunks of
+// kChunk tokens: this one selects each chunk's experts, counts its pairs per
+// expert and ranks them within the chunk (as moe_route_kernel does); the next
+// adds up the counts and places the pairs. (Three launches, with ranks from
+// ballots over all experts: E = 64, k = 8, 700 tokens 122 us, now 16; E = 8, k = 2,
+// 2048 tokens 18 us, now 11.)
+__global__ __launch_bounds__(8 * kChunk) void moe_topk_kernel(const float* __restrict__ logits, int T, int E, int k,
+                                                              int32_t* ids, float* wts, int32_t* u_ids, float* u_w,
+                                                              int32_t* blockcnt, int32_t* rank) {
+  constexpr int kWords = kChunk / 32;
+  __shared__ uint32_t mask[kMaxE * (kWords + 1)];
+  __shared__ float s_log[kChunk * (kThreadTopkMaxE + 1)];
+  __shared__ uint8_t s_ids[kChunk * kMaxK];
   const int tid = threadIdx.x;
-  if (tid < kMaxE) cnt[tid] = 0;
-  const int t0 = blockIdx.x * 256;
+  const int t0 = blockIdx.x * kChunk, n = min(kChunk, T - t0);
+  if (tid < E * (kWords + 1)) mask[tid] = 0;
+  auto put = [&](int t, int j, int e, float w) {  // slot j of the chunk's token t
+    const size_t i = (size_t)(t0 + t) * k + j;
+    ids[i] = e;
+    wts[i] = w;
+    s_ids[t * k + j] = static_cast<uint8_t>(e);
+    if (u_ids) u_ids[i] = e;
+    if (u_w) u_w[i] = w;
+    atomicOr(&mask[e * (kWords + 1) + (t >> 5)], 1u << (t & 31));
+  };
   if (E <= kThreadTopkMaxE) {
     const int ls = E | 1;
-    stage_logits<256>(logits + (size_t)t0 * E, min(256, T - t0), E, ls, s_log, tid);
+    stage_logits<8 * kChunk>(logits + (size_t)t0 * E, n, E, ls, s_log, tid);
     __syncthreads();
-    const int t = t0 + tid;
-    if (t < T) {
+    if (tid < n) {
       int sid[kMaxK];
       float w[kMaxK];
       topk_token(s_log + tid * ls, E, k, sid, w);
-      for (int j = 0; j < k; ++j) {
-        ids[t * k + j] = sid[j];
-        wts[t * k + j] = w[j];
-        if (u_ids) u_ids[t * k + j] = sid[j];
-        if (u_w) u_w[t * k + j] = w[j];
-        atomicAdd(&cnt[sid[j]], 1);
-      }
+      for (int j = 0; j < k; ++j) put(tid, j, sid[j], w[j]);
     }
   } else {
     __syncthreads();
-    for (int c = 0; c < 256 && t0 + c < T; c += 32) {
-      const int t = t0 + c + (tid >> 3), j = tid & 7;
-      int e;
-      float w;
-      topk_lanes(logits + (size_t)t * E, t < T, E, k, j, tid & 63, &e, &w);
-      if (t < T && j < k) {
-        ids[t * k + j] = e;
-        wts[t * k + j] = w;
-        if (u_ids) u_ids[t * k + j] = e;
-        if (u_w) u_w[t * k + j] = w;
-        atomicAdd(&cnt[e], 1);
-      }
-    }
+    const int t = tid >> 3, j = tid & 7;
+    int e;
+    float w;
+    topk_lanes(logits + (size_t)(t0 + t) * E, t < n, E, k, j, tid & 63, &e, &w);
+    if (t < n && j < k) put(t, j, e, w);
   }
   __syncthreads();
-  if (tid < E) blockcnt[(size_t)blockIdx.x * E + tid] = cnt[tid];
+  if (tid < E) {
+    int cnt = 0;
+    for (int w = 0; w < kWords; ++w) cnt += __popc(mask[tid * (kWords + 1) + w]);
+    blockcnt[(size_t)blockIdx.x * E + tid] = cnt;
+  }
+  if (tid < n * k) {
+    const int t = tid / k;
+    const uint32_t* m = mask + s_ids[tid] * (kWords + 1);
+    int r = __popc(m[t >> 5] & ((1u << (t & 31)) - 1u));
+    for (int w = 0; w < (t >> 5); ++w) r += __popc(m[w]);
+    rank[(size_t)t0 * k + tid] = r;
+  }
 }
 
-__global__ __launch_bounds__(64) void moe_offsets_kernel(const int32_t* __restrict__ blockcnt, int nblk, int E,
-                                                          int bm, int32_t* offsets, int32_t* u_offsets,
-                                                          int32_t* tile_map, int32_t* num_tiles,
-                                                          int32_t* blockbase) {
-  __shared__ int off[kMaxE + 1];
-  const int lane = threadIdx.x;
-  int sum = 0;
+// Places a chunk's pairs: every work-group adds up all chunks' counts (8 groups
+// of 64 lanes, lane e for expert e), the first one writes offsets and tile map.
+// `pos` holds the ranks within the chunk on entry.
+__global__ __launch_bounds__(8 * kChunk) void moe_place_kernel(const int32_t* __restrict__ ids,
+                                                               const int32_t* __restrict__ blockcnt, int nblk, int T,
+                                                               int E, int k, int bm, int32_t* offsets,
+                                                               int32_t* u_offsets, int32_t* tile_map,
+                                                               int32_t* num_tiles, int32_t* sorted, int32_t* pos,
+                                                               int32_t* u_sorted) {
+  constexpr int kParts = 8 * kChunk / 64;
+  __shared__ int s_tot[kParts][64], s_pre[kParts][64];
+  __shared__ int off[kMaxE + 1], base[kMaxE];
+  const int tid = threadIdx.x, lane = tid & 63, part = tid >> 6, blk = blockIdx.x;
+  const int n = min(kChunk, T - blk * kChunk) * k;
+  const size_t i = (size_t)blk * kChunk * k + tid;
+  const int e = tid < n ? ids[i] : 0, r = tid < n ? pos[i] : 0;
+  int tot = 0, pre = 0;
   if (lane < E) {
-    for (int b = 0; b < nblk; ++b) {
-      blockbase[(size_t)b * E + lane] = sum;
-      sum += blockcnt[(size_t)b * E + lane];
+#pragma unroll 4
+    for (int b = part; b < nblk; b += kParts) {
+      const int v = blockcnt[(size_t)b * E + lane];
+      tot += v;
+      pre += b < blk ? v : 0;
     }
   }
-  plan_tiles(sum, lane, E, bm, off, offsets, u_offsets, tile_map, num_tiles);
-}
-
-__global__ __launch_bounds__(256) void moe_rank_kernel(const int32_t* __restrict__ ids, int T, int E, int k,
-                                                       const int32_t* __restrict__ offsets,
-                                                       const int32_t* __restrict__ blockbase, int32_t* sorted,
-                                                       int32_t* pos, int32_t* u_sorted) {
-  __shared__ int wcnt[4][kMaxE];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int t = blockIdx.x * 256 + tid;
-  const bool valid = t < T;
-  int my_e[kMaxK], pre[kMaxK];
-  for (int j = 0; j < k; ++j) my_e[j] = valid ? ids[t * k + j] : -1;
-  chunk_ranks(my_e, valid, E, k, wave, lane, pre, wcnt);
+  s_tot[part][lane] = tot;
+  s_pre[part][lane] = pre;
   __syncthreads();
-  if (valid) {
-    for (int j = 0; j < k; ++j) {
-      const int e = my_e[j];
-      int r = blockbase[(size_t)blockIdx.x * E + e] + pre[j];
-      for (int w = 0; w < wave; ++w) r += wcnt[w][e];
-      const int pidx = offsets[e] + r;
-      sorted[pidx] = t * k + j;
-      pos[t * k + j] = pidx;
-      if (u_sorted) u_sorted[pidx] = t * k + j;
+  if (tid < 64) {
+    tot = pre = 0;
+#pragma unroll
+    for (int q = 0; q < kParts; ++q) {
+      tot += s_tot[q][lane];
+      pre += s_pre[q][lane];
     }
+    plan_tiles(tot, lane, E, bm, blk == 0, off, offsets, u_offsets, tile_map, num_tiles);
+    base[lane] = pre;
+  }
+  __syncthreads();
+  if (tid < n) {
+    const int pidx = off[e] + base[e] + r;
+    sorted[pidx] = (int)i;
+    pos[i] = pidx;
+    if (u_sorted) u_sorted[pidx] = (int)i;
   }
 }
 
@@ -534,15 +524,13 @@ hipError_t launch_moe_route(const aflex_ffn_args& f, void* route_ws, hipStream_t
                                             f.sorted_pairs);
     return hipGetLastError();
   }
-  const int nblk = (f.T + 255) / 256;
+  const int nblk = (f.T + kChunk - 1) / kChunk;
   int32_t* blockcnt = reinterpret_cast<int32_t*>(w + L.blockcnt);
-  int32_t* blockbase = reinterpret_cast<int32_t*>(w + L.blockbase);
-  moe_topk_kernel<<<nblk, 256, 0, stream>>>(f.router_logits, f.T, f.E, f.k, ids, wts, f.topk_ids, f.topk_w,
-                                            blockcnt);
-  moe_offsets_kernel<<<1, 64, 0, stream>>>(blockcnt, nblk, f.E, L.bm, offsets, f.expert_offsets, tile_map,
-                                            num_tiles, blockbase);
-  moe_rank_kernel<<<nblk, 256, 0, stream>>>(ids, f.T, f.E, f.k, offsets, blockbase, sorted, pos,
-                                            f.sorted_pairs);
+  moe_topk_kernel<<<nblk, 8 * kChunk, 0, stream>>>(f.router_logits, f.T, f.E, f.k, ids, wts, f.topk_ids, f.topk_w,
+                                                   blockcnt, pos);
+  moe_place_kernel<<<nblk, 8 * kChunk, 0, stream>>>(ids, blockcnt, nblk, f.T, f.E, f.k, L.bm, offsets,
+                                                    f.expert_offsets, tile_map, num_tiles, sorted, pos,
+                                                    f.sorted_pairs);
   return hipGetLastError();
 }
 

@@ -14,7 +14,8 @@ DEV = "cuda:0"
 # even split over three tiles; k: one, two and three k-steps and past one turn
 # of the ring; columns: a quarter, three quarters and one and a quarter tiles
 LINEAR = [(129, 64, 64), (143, 128, 192), (145, 192, 320), (255, 256, 256), (256, 320, 448), (257, 384, 64),
-          (300, 640, 256), (513, 704, 320), (2305, 192, 512)]
+          (300, 640, 256), (513, 704, 320), (2305, 192, 512),
+          (2305, 2048, 320)]  # ten row tiles (a group of 8 and one of 2) in several k-splits
 
 
 @pytest.mark.parametrize("T,K,N", LINEAR)
@@ -34,9 +35,10 @@ def test_swiglu_tile_edges(gpu_lib, T, H, I):
     check_rows(y, oracle.swiglu_ffn(x, w.w_gate, w.w_up, w.w_down), what=f"swiglu {T}x{H}x{I}")
 
 
-@pytest.mark.parametrize("T,H,I,E,k", [(290, 64, 64, 2, 1), (400, 192, 128, 2, 2), (650, 128, 192, 4, 2)])
+@pytest.mark.parametrize("T,H,I,E,k", [(290, 64, 64, 2, 1), (400, 192, 128, 2, 2), (650, 128, 192, 4, 2),
+                                         (2700, 64, 1088, 2, 1)])
 def test_moe_even_row_tiles(gpu_lib, T, H, I, E, k):
-    """Experts of one, two and three row tiles, whose rows are split evenly."""
+    """Experts of one, two, three and more than eight row tiles, whose rows are split evenly."""
     x, w, logits = synth.custom_ffn(33, T, H, I, E=E)
     logits[:, 0] += 0.7  # an uneven load
     y = aflex.moe_ffn(x.to(DEV), w.to(DEV), logits.to(DEV), k).cpu()

@@ -1,6 +1,6 @@
 """MoE routing: the chosen experts, weights, offsets and pair order, exactly, at
-the edges of its three paths (one thread or eight lanes per token, one
-work-group up to 512 tokens), with ties, infinities and skewed loads."""
+the edges of its paths (one thread or eight lanes per token; one work-group up
+to 512 tokens, chunks of 64 beyond, more chunks than groups that add them up), with ties, infinities and skewed loads."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +13,7 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("E,k", [(8, 2), (16, 8), (17, 1), (33, 8), (63, 4), (64, 8)])
-@pytest.mark.parametrize("T", [1, 33, 64, 65, 512, 513])
+@pytest.mark.parametrize("T", [1, 33, 64, 65, 512, 513, 640, 1025, 2177])
 def test_routing_exact(gpu_lib, T, E, k):
     rng = np.random.default_rng([T, E, k])
     logits = np.round(rng.standard_normal((T, E)).astype(np.float32) * 2) / 2  # many ties
