@@ -31,9 +31,11 @@ struct FfnPlan {
 // Up to 32 rows a tile covers a typical expert (its weights are streamed once,
 // non-temporally); up to 48 rows 64-row tiles, two work-groups per CU (an
 // expert's second tile re-reads its weights from L2; at 32 rows per expert
-// 535 us against 611 us with 128-row tiles); up to 144 rows the 8-wave
-// 128-row tile; beyond, the 256-row shape (Mixtral shapes, 128 rows per
-// expert: 828 us with 128-row tiles, 857 with 256; 160 rows: 936 and 888).
+// 535 us against 611 us with 128-row tiles); up to 96 rows the 8-wave 128-row
+// tile; beyond, the 256-row shape, which holds an expert of up to 256 rows in
+// one tile where more and more experts take two of 128 (Mixtral shapes, 80 rows
+// per expert: 510 us with 128-row tiles, 539 with 256; 95: 533 and 547; 112: 628
+// and 564; 127: 707 and 581; 144: 842 and 600).
 //
 // An expert's rows are split evenly over its row tiles (tile_rows below), so
 // one just over a multiple of 256 rows has no nearly empty tile that streams all
@@ -41,18 +43,18 @@ struct FfnPlan {
 inline int pick_bm(double rows_per_expert) {
   if (rows_per_expert * 1.3 <= 32) return 32;
   if (rows_per_expert <= 48) return 64;
-  if (rows_per_expert <= 144) return 128;
+  if (rows_per_expert <= 96) return 128;
   return 256;
 }
 
 // Rows per tile when n rows take the fewest tiles of at most bm rows: even
-// shares, in whole 16-row blocks, for the 256-row tiles, whose waves multiply
-// only filled blocks and share them evenly (Mixtral T = 2048, 472-541 rows per
-// expert: three tiles of 176 rows instead of 256 + 256 + 29); else bm.
+// shares, in whole 32-row blocks, for the 256-row tiles, which multiply only
+// filled blocks (Mixtral T = 2048, 472-541 rows per expert: 192 + 192 + 157
+// instead of 256 + 256 + 29); else bm.
 __host__ __device__ inline int tile_rows(int n, int bm) {
   if (bm < 256 || n <= bm) return bm;
-  const int tiles = (n + bm - 1) / bm, blocks = (n + 15) / 16;
-  return (blocks + tiles - 1) / tiles * 16;
+  const int tiles = (n + bm - 1) / bm, blocks = (n + 31) / 32;
+  return (blocks + tiles - 1) / tiles * 32;
 }
 
 // Split K of the down GEMM, keeping at least `min_steps` 64-wide k-steps per

@@ -17,7 +17,7 @@
 //
 // Rows: 16-row block 2 i + wm of the tile is block i of the waves with row index
 // wm, so a partly filled tile is shared evenly by the waves; only filled blocks
-// are loaded and multiplied (in instances of 8, 6, 4 or 2 blocks per wave).
+// are loaded and multiplied (in instances of 2 to 8 blocks per wave).
 //
 // Measured (dense SwiGLU, H = 5120, I = 25600; the eight-wave 32x32x16 tiles
 // with two 64-wide stages before): T = 4096 2870 -> 2350 us (1.12 -> 1.37
@@ -229,12 +229,18 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
   };
   const int rows = x.row1 - x.row0;
   if (nk > 0) {
-    if (rows > 192)
+    if (rows > 224)
       kloop(std::integral_constant<int, 8>{});
-    else if (rows > 128)
+    else if (rows > 192)
+      kloop(std::integral_constant<int, 7>{});
+    else if (rows > 160)
       kloop(std::integral_constant<int, 6>{});
-    else if (rows > 64)
+    else if (rows > 128)
+      kloop(std::integral_constant<int, 5>{});
+    else if (rows > 96)
       kloop(std::integral_constant<int, 4>{});
+    else if (rows > 64)
+      kloop(std::integral_constant<int, 3>{});
     else
       kloop(std::integral_constant<int, 2>{});
   }

@@ -331,8 +331,8 @@ __global__ __launch_bounds__(512) void moe_route_kernel(const float* __restrict_
 // kChunk tokens: this one selects each chunk's experts, counts its pairs per
 // expert and ranks them within the chunk (as moe_route_kernel does); the next
 // adds up the counts and places the pairs. (Three launches, with ranks from
-// ballots over all experts: E = 64, k = 8, 700 tokens 122 us, now 16; E = 8, k = 2,
-// 2048 tokens 18 us, now 11.)
+// ballots over all experts: E = 64, k = 8, 700 tokens 122 us, now 13; E = 8, k = 2,
+// 2048 tokens 18 us, now 12.)
 __global__ __launch_bounds__(8 * kChunk) void moe_topk_kernel(const float* __restrict__ logits, int T, int E, int k,
                                                               int32_t* ids, float* wts, int32_t* u_ids, float* u_w,
                                                               int32_t* blockcnt, int32_t* rank) {
