@@ -53,14 +53,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 }
 
 size_t swiglu_workspace_bytes(const aflex_ffn_args& f) {
-  const FfnPlan pl = plan_dense(f.T, f.H, f.I);
+  const FfnPlan pl = plan_dense(f.T, f.H, f.I, f.I);
   size_t b = align_up((size_t)f.T * f.I * 2, 256);
   if (pl.down_splits > 1) b += align_up((size_t)pl.down_splits * f.T * f.H * 4, 256);
   return b;
 }
 
 hipError_t launch_swiglu(const aflex_ffn_args& f, void* ws, hipStream_t stream) {
-  const FfnPlan pl = plan_dense(f.T, f.H, f.I);
+  const FfnPlan pl = plan_dense(f.T, f.H, f.I, f.I);
   uint16_t* h = static_cast<uint16_t*>(ws);
   float* P = reinterpret_cast<float*>(static_cast<char*>(ws) + align_up((size_t)f.T * f.I * 2, 256));
 
@@ -81,8 +81,7 @@ hipError_t launch_swiglu(const aflex_ffn_args& f, void* ws, hipStream_t stream) 
   g.mt_major = 0;
   g.C = h;
   g.ldc = f.I;
-  const bool once = f.T <= pl.bm;
-  hipError_t e = launch_gate_up(pl.bm, once, g, stream);
+  hipError_t e = launch_gate_up(pl.bm, pl.nt, g, stream);
   if (e != hipSuccess) return e;
 
   GemmParams d = {};
@@ -104,7 +103,7 @@ hipError_t launch_swiglu(const aflex_ffn_args& f, void* ws, hipStream_t stream) 
   d.P = P;
   d.p_split_stride = (long long)f.T * f.H;
   d.ldp = f.H;
-  e = launch_down(pl.bm, pl.down_splits > 1, once, d, stream);
+  e = launch_down(pl.bm, pl.down_splits > 1, pl.nt, d, stream);
   if (e != hipSuccess || pl.down_splits == 1) return e;
   const long long n4 = (long long)f.T * f.H / 4;
   ProfScope ps("splitk_reduce", stream);
@@ -117,12 +116,12 @@ hipError_t launch_swiglu(const aflex_ffn_args& f, void* ws, hipStream_t stream) 
 // the same fixed-order reduction (bf16 out directly when a single split
 // suffices); the optional residual is added before the one rounding.
 size_t linear_workspace_bytes(const aflex_linear_args& l) {
-  const FfnPlan pl = plan_dense(l.T, l.N, l.K);
+  const FfnPlan pl = plan_dense(l.T, l.N, l.K, 0);
   return pl.down_splits > 1 ? align_up((size_t)pl.down_splits * l.T * l.N * 4, 256) : 256;
 }
 
 hipError_t launch_linear(const aflex_linear_args& l, void* ws, hipStream_t stream, const uint16_t* residual) {
-  const FfnPlan pl = plan_dense(l.T, l.N, l.K);
+  const FfnPlan pl = plan_dense(l.T, l.N, l.K, 0);
   float* P = static_cast<float*>(ws);
   GemmParams d = {};
   d.A = l.x;
@@ -144,7 +143,7 @@ hipError_t launch_linear(const aflex_linear_args& l, void* ws, hipStream_t strea
   d.p_split_stride = (long long)l.T * l.N;
   d.ldp = l.N;
   d.R = residual;
-  hipError_t e = launch_down(pl.bm, pl.down_splits > 1, l.T <= pl.bm, d, stream);
+  hipError_t e = launch_down(pl.bm, pl.down_splits > 1, pl.nt, d, stream);
   if (e != hipSuccess || pl.down_splits == 1) return e;
   const long long n4 = (long long)l.T * l.N / 4;
   ProfScope ps("splitk_reduce", stream);

@@ -7,9 +7,7 @@
 namespace aflex {
 
 // Output columns per gate/up tile (x2 weight rows) and per down tile. The
-// 128- and 256-row tiles are the 8-wave 32x32x16 MFMA shapes (one work-group
-// per CU); dense GEMMs take 128-row tiles for 33 ... 128 tokens (measured:
-// T = 128 262 -> 211 us against 256-row tiles).
+// 128- and 256-row tiles take a CU's whole LDS (one work-group per CU).
 inline int gate_bn(int bm) { return bm >= 128 ? 128 : 64; }
 
 inline int down_bn(int bm) { return bm >= 128 ? 256 : 128; }
@@ -17,12 +15,13 @@ inline int down_bn(int bm) { return bm >= 128 ? 256 : 128; }
 // work-group per CU, so one round of the chip; smaller tiles two per CU.
 constexpr int kOneWgPerCuTarget = 256;
 inline int down_target(int bm) { return bm >= 128 ? kOneWgPerCuTarget : (bm == 64 ? 2048 : 512); }
-// Work-groups resident on the 256 CUs at once: one per CU for the 8-wave
-// tiles (the whole LDS), two for the 4-wave tiles.
+// Work-groups resident on the 256 CUs at once: one per CU for the 128- and
+// 256-row tiles (the whole LDS), two for the smaller ones.
 inline int concurrent_wgs(int bm) { return bm >= 128 ? 256 : 512; }
 
 struct FfnPlan {
-  int bm;           // rows per m-tile: 32, 128 or 256
+  int bm;           // rows per m-tile: 32, 64, 128 or 256
+  bool nt;          // weight loads are non-temporal
   int down_splits;  // split-K factor of the down GEMM
   int down_kps;     // k elements per split (multiple of 64)
 };
@@ -92,19 +91,52 @@ inline void plan_splits(int base_tiles, int K, int target, int slots, int min_st
   *kps = steps * 64;
 }
 
-inline FfnPlan plan_dense(int T, int H, int I) {
+// Weights up to this size stay in the 256 MB Infinity Cache for a next call with
+// them (the other microbatches of a layer, a small model), so their loads are
+// ordinary; larger ones, where each byte is read by one work-group, load
+// non-temporally. Linear of 8192 x 5120 (84 MB), called again and again, T = 64:
+// 28.4 us non-temporal, 23.7 ordinary; SwiGLU of 5120 x 25600 (786 MB), T = 200:
+// 201 and 211.
+constexpr long long kKeepWeightBytes = 160ll << 20;
+
+// Work-groups of a GEMM below which smaller tiles, of which there are more, are
+// faster although they read more (256 CUs). SwiGLU 4096 x 14336, 128-row tiles
+// (112 work-groups) and 64-row tiles: T = 40 86 and 71 us; 256- (112) and 128-row
+// tiles: T = 256 145 and 124 us. 5120 x 25600 (200 work-groups): T = 40 143 and
+// 157 us; 2048 x 22400 (175): T = 200 91 and 113 us.
+constexpr int kFewWorkGroups = 160;
+
+// Plan of a linear layer [N, K] (gate_cols = 0) or of a SwiGLU whose down matrix
+// is [N, K] and whose gate and up matrices are [gate_cols, N]: the largest tile
+// of 256, 128 or 64 rows whose first GEMM has enough work-groups; 32 rows up to 32
+// tokens. Up to 128 tokens, weights that stay cached take 64-row tiles, two
+// work-groups per CU (linear 8192 x 5120, T = 128: 28.5 -> 25.1 us); larger ones
+// only where one tile holds all rows (4096 x 14336, T = 128: 105 us with 128-row
+// tiles, 108 with 64). Small matrices gain most: SwiGLU 512 x 1408, T = 700 46 ->
+// 21 us, linear 2048 x 1024, T = 200 20.5 -> 11.3.
+inline FfnPlan plan_dense(int T, int N, int K, int gate_cols) {
+  const bool keep = (gate_cols ? 3ll : 1ll) * N * K * 2 <= kKeepWeightBytes;
   FfnPlan pl;
-  pl.bm = T <= 32 ? 32 : (T <= 128 ? 128 : 256);
-  const int mtiles = (T + pl.bm - 1) / pl.bm;
-  const int ntiles = (H + down_bn(pl.bm) - 1) / down_bn(pl.bm);
-  plan_splits(mtiles * ntiles, I, down_target(pl.bm), concurrent_wgs(pl.bm), 8, &pl.down_splits, &pl.down_kps);
+  auto try_bm = [&](int bm) {  // returns the work-groups of the first GEMM
+    const int mtiles = (T + bm - 1) / bm;
+    const int ntiles = (N + down_bn(bm) - 1) / down_bn(bm);
+    pl.bm = bm;
+    plan_splits(mtiles * ntiles, K, down_target(bm), concurrent_wgs(bm), 8, &pl.down_splits, &pl.down_kps);
+    return (long long)mtiles * (gate_cols ? (gate_cols + gate_bn(bm) - 1) / gate_bn(bm) : ntiles * pl.down_splits);
+  };
+  if (T <= 32) {
+    try_bm(32);
+  } else if (T > 128) {
+    if (try_bm(256) <= kFewWorkGroups && try_bm(128) <= kFewWorkGroups) try_bm(64);
+  } else if (keep || (try_bm(128) <= kFewWorkGroups && T <= 64)) {
+    try_bm(64);
+  }
+  pl.nt = !keep && T <= pl.bm;
   return pl;
 }
 
-// `once`: the call has (dense) or is expected to have (MoE, from the average
-// rows per expert) a single row tile per weight matrix, so every weight byte
-// is read once and its loads can be non-temporal.
-hipError_t launch_gate_up(int bm, bool once, const GemmParams& g, hipStream_t stream);
-hipError_t launch_down(int bm, bool f32_partials, bool once, const GemmParams& g, hipStream_t stream);
+// `nt`: weight loads are non-temporal.
+hipError_t launch_gate_up(int bm, bool nt, const GemmParams& g, hipStream_t stream);
+hipError_t launch_down(int bm, bool f32_partials, bool nt, const GemmParams& g, hipStream_t stream);
 
 }  // namespace aflex

@@ -37,19 +37,21 @@ struct MoeLayout {
   size_t ids, wts, offsets, sorted, pos, tile_map, num_tiles, blockcnt, route_total;
   size_t h, P, expert_total;
   int bm, max_tiles, down_splits, down_kps;
-  // 64- and 128-row tiles: experts' rows are expected to fit one tile
-  // (average rows per expert x 1.3 <= bm, the margin pick_bm uses for 32-row
-  // tiles), so each expert's weights are streamed once and load
-  // non-temporally (measured 4-5% faster at 32-48 rows per expert on 64-row
-  // tiles, 11% at 64 rows per expert on 128-row tiles).
-  bool once;
+  // Experts' rows are expected to fit one tile (average rows per expert x 1.3
+  // <= bm, the margin pick_bm uses for 32-row tiles; always at 32 rows), so each
+  // expert's weights are streamed once and, where they are more than stays
+  // cached, load non-temporally (4-5% faster at 32-48 rows per expert on 64-row
+  // tiles, 11% at 64 on 128-row tiles, 5-6% at 112-190 on 256-row tiles: T = 509
+  // 580 -> 550 us).
+  bool once, nt;
 };
 
 static MoeLayout moe_layout(const aflex_ffn_args& f) {
   MoeLayout L;
   const size_t pairs = (size_t)f.T * f.k;
   L.bm = pick_bm((double)pairs / f.E);
-  L.once = (L.bm == 64 || L.bm == 128) && (double)pairs / f.E * 1.3 <= (double)L.bm;
+  L.once = L.bm == 32 || (double)pairs / f.E * 1.3 <= (double)L.bm;
+  L.nt = L.once && 6ll * f.E * f.H * f.I > kKeepWeightBytes;
   L.max_tiles = (int)((pairs + L.bm - 1) / L.bm) + f.E;
   const int ntiles = (f.H + down_bn(L.bm) - 1) / down_bn(L.bm);
   // The tile count is a worst case here (the routing stays on the device):
@@ -579,11 +581,11 @@ hipError_t launch_moe_experts(const aflex_ffn_args& f, void* route_ws, void* exp
   // us). Otherwise an expert's m-tiles stay adjacent, so its overflow tiles
   // re-read the weights from L2 (the expert-major order took 512 tokens from
   // 745 to 820 us).
-  const int order = (L.bm == 32 || L.once) ? 2 : 0;
+  const int order = L.once ? 2 : 0;
   g.mt_major = order;
   g.C = h;
   g.ldc = f.I;
-  e = launch_gate_up(L.bm, L.once, g, stream);
+  e = launch_gate_up(L.bm, L.nt, g, stream);
   if (e != hipSuccess) return e;
 
   const long long pairs = (long long)f.T * f.k;
@@ -610,7 +612,7 @@ hipError_t launch_moe_experts(const aflex_ffn_args& f, void* route_ws, void* exp
   d.P = P;
   d.p_split_stride = pairs * f.H;
   d.ldp = f.H;
-  e = launch_down(L.bm, true, L.once, d, stream);
+  e = launch_down(L.bm, true, L.nt, d, stream);
   if (e != hipSuccess) return e;
 
   dim3 grid(f.T, (f.H / 4 + 255) / 256);

@@ -1,0 +1,70 @@
+"""GEMM tile plans: each tile height at its edges, with weights small enough to
+stay cached (ordinary loads) and larger ones (non-temporal loads), against
+float64."""
+import functools
+
+import pytest
+import torch
+
+from paper_2608_01891_amd import aflex, synth
+from tests.parity import check_rows
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@functools.lru_cache(maxsize=1)
+def _linear(K, N):
+    return (synth.normal_tensor(51, 1, (300, K)).to(DEV),
+            synth.normal_tensor(51, 2, (N, K), synth.WEIGHT_SIGMA).to(DEV))
+
+
+@functools.lru_cache(maxsize=1)
+def _ffn(H, I, E):
+    x, w, logits = synth.custom_ffn(52, 512, H, I, E=E)
+    return x.to(DEV), w.to(DEV), None if logits is None else logits.to(DEV)
+
+
+def _swiglu64(x, w):
+    g, u = x @ w.w_gate.double().t(), x @ w.w_up.double().t()
+    return (g / (1.0 + torch.exp(-g)) * u) @ w.w_down.double().t()
+
+
+# 168 MB of weights (past what is kept): 64-row tiles for few work-groups, else 128; 4 MB: 64-row tiles
+# up to 128 tokens and where larger ones are few
+@pytest.mark.parametrize("T", [1, 32, 33, 64, 65, 128, 129, 256, 257])
+@pytest.mark.parametrize("K,N", [(8192, 10304), (1024, 1984)])
+def test_linear(gpu_lib, T, K, N):
+    x, w = _linear(K, N)
+    x = x[:T]
+    y = torch.full((T + 1, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+    aflex.linear(x, w, y=y[:T])
+    check_rows(y[:T].cpu(), (x.double() @ w.double().t()).cpu(), what=f"linear {T}x{K}x{N}")
+    assert torch.isnan(y[T]).all()
+
+
+# first GEMMs of few (112, at 256 rows) and of enough work-groups; 176, 352 and 2 MB
+@pytest.mark.parametrize("T", [31, 33, 64, 100, 129, 256, 290])
+@pytest.mark.parametrize("H,I", [(2048, 14336), (2752, 21376), (576, 640)])
+def test_swiglu(gpu_lib, T, H, I):
+    x, w, _ = _ffn(H, I, 0)
+    x = x[:T]
+    check_rows(aflex.ffn_swiglu(x, w).cpu(), _swiglu64(x.double(), w).cpu(), what=f"swiglu {T}x{H}x{I}")
+
+
+# rows per expert: 32-, 64-, 128- and 256-row tiles, experts over and under one tile; 264 and 2 MB
+@pytest.mark.parametrize("T", [30, 80, 190, 200, 380, 500])
+@pytest.mark.parametrize("H,I", [(2048, 5376), (256, 320)])
+def test_moe(gpu_lib, T, H, I):
+    E, k = 4, 2
+    x, w, logits = _ffn(H, I, E)
+    x, logits = x[:T], logits[:T].contiguous()
+    y = aflex.moe_ffn(x, w, logits, k)
+    top, ids = torch.sort(logits.double(), dim=-1, descending=True, stable=True)
+    ids, p = ids[:, :k], torch.softmax(top[:, :k], -1)
+    ref = torch.zeros(T, H, dtype=torch.float64, device=DEV)
+    for e in range(E):
+        t, j = torch.nonzero(ids == e, as_tuple=True)
+        one = type("W", (), {"w_gate": w.w_gate[e], "w_up": w.w_up[e], "w_down": w.w_down[e]})
+        ref[t] += p[t, j, None] * _swiglu64(x[t].double(), one)
+    check_rows(y.cpu(), ref.cpu(), what=f"moe {T}x{H}x{I}")
