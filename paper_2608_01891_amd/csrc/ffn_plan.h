@@ -105,11 +105,16 @@ constexpr long long kKeepWeightBytes = 160ll << 20;
 // tiles: T = 256 145 and 124 us. 5120 x 25600 (200 work-groups): T = 40 143 and
 // 157 us; 2048 x 22400 (175): T = 200 91 and 113 us.
 constexpr int kFewWorkGroups = 160;
+// The same for MoE calls, whose tile count is an estimate: few enough that tiles
+// of half the height still fit one round. E = 8, 512 x 512, k = 2, T = 1000: 55 ->
+// 32 us with 64-row tiles; E = 4, 1024 x 1024, T = 300: 56 -> 31; but with 144
+// work-groups (E = 3, 4096 x 3008, T = 600) 128-row tiles 178, 256-row tiles 129 us.
+constexpr int kFewGroupedWorkGroups = 112;
 
 // Plan of a linear layer [N, K] (gate_cols = 0) or of a SwiGLU whose down matrix
 // is [N, K] and whose gate and up matrices are [gate_cols, N]: the largest tile
-// of 256, 128 or 64 rows whose first GEMM has enough work-groups; 32 rows up to 32
-// tokens. Up to 128 tokens, weights that stay cached take 64-row tiles, two
+// of 256, 128 or 64 rows whose first GEMM has enough work-groups, unless the next
+// smaller takes a second round of them; 32 rows up to 32 tokens. Up to 128 tokens, weights that stay cached take 64-row tiles, two
 // work-groups per CU (linear 8192 x 5120, T = 128: 28.5 -> 25.1 us); larger ones
 // only where one tile holds all rows (4096 x 14336, T = 128: 105 us with 128-row
 // tiles, 108 with 64). Small matrices gain most: SwiGLU 512 x 1408, T = 700 46 ->
@@ -127,7 +132,13 @@ inline FfnPlan plan_dense(int T, int N, int K, int gate_cols) {
   if (T <= 32) {
     try_bm(32);
   } else if (T > 128) {
-    if (try_bm(256) <= kFewWorkGroups && try_bm(128) <= kFewWorkGroups) try_bm(64);
+    if (try_bm(256) <= kFewWorkGroups) {
+      const long long n128 = try_bm(128);
+      if (n128 > concurrent_wgs(128))
+        try_bm(256);
+      else if (n128 <= kFewWorkGroups && try_bm(64) > concurrent_wgs(64))
+        try_bm(128);
+    }
   } else if (keep || (try_bm(128) <= kFewWorkGroups && T <= 64)) {
     try_bm(64);
   }

@@ -50,6 +50,9 @@ static MoeLayout moe_layout(const aflex_ffn_args& f) {
   MoeLayout L;
   const size_t pairs = (size_t)f.T * f.k;
   L.bm = pick_bm((double)pairs / f.E);
+  const long long avg = ((long long)pairs + f.E - 1) / f.E;  // rows per expert
+  auto work_groups = [&](int bm) { return f.E * ((avg + bm - 1) / bm) * ((f.I + gate_bn(bm) - 1) / gate_bn(bm)); };
+  while (L.bm > 64 && work_groups(L.bm) <= kFewGroupedWorkGroups) L.bm /= 2;
   L.once = L.bm == 32 || (double)pairs / f.E * 1.3 <= (double)L.bm;
   L.nt = L.once && 6ll * f.E * f.H * f.I > kKeepWeightBytes;
   L.max_tiles = (int)((pairs + L.bm - 1) / L.bm) + f.E;
