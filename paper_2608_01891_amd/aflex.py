@@ -252,7 +252,12 @@ def _run(name, args, key, device, ws, stream):
     stream. The workspace at hand is tried first: the library rejects one that is
     too small (or missing) before it launches anything, and only then is the size
     queried. (Two library calls, a Stream object and keyword-built argument
-    blocks per call held a tiny layer's attention, 5 us on the GPU, at 11.3 us.)"""
+    blocks per call held a tiny layer's attention, 5 us on the GPU, at 11.3 us.)
+
+    Tensors that are not on a GPU are refused here, before any library call: a
+    kernel would read and write the host's addresses."""
+    if device.type != "cuda":
+        raise ValueError(f"{name}: expected tensors on a cuda device, but got: {device}")
     if ws is None:
         ws = _default_ws.get(key)
         if ws is None:

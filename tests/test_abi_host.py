@@ -6,7 +6,7 @@ import os
 
 import pytest
 
-from paper_2608_01891_amd import aflex
+from paper_2608_01891_amd import aflex, synth
 
 FAKE = 0x10000000  # aligned, never dereferenced: validation fails before any launch
 
@@ -246,3 +246,32 @@ def test_layer_step_validation(lib, case, status):
     elif case == "bad_eps":
         la.eps = -1.0
     assert _layer_status(lib, a, f, la, L=L) == status
+
+
+@pytest.mark.parametrize("op", ["attn_decode", "ffn_swiglu", "moe_ffn", "linear", "moe_block"])
+@pytest.mark.parametrize("ws", [None, aflex.Workspace])
+def test_host_tensors_are_refused_before_any_library_call(lib, monkeypatch, op, ws):
+    """Each operator that takes a workspace raises for tensors in host memory,
+    whether its workspace is the default or the caller's, and launches nothing."""
+    calls = []
+
+    class Stub:
+        def __getattr__(self, name):
+            return lambda *a: calls.append(name) or aflex.OK
+
+    monkeypatch.setattr(aflex, "_lib", Stub())
+    monkeypatch.setattr(aflex, "_stream", lambda s: 0)
+    monkeypatch.setattr(aflex, "_default_ws", {})
+    ws = ws and ws()
+    w = synth.tiny_layer()
+    x, moe, logits = synth.custom_ffn(1, 4, 64, 64, E=4)
+    call = {
+        "attn_decode": lambda: aflex.attn_decode(w.attn, ws=ws),
+        "ffn_swiglu": lambda: aflex.ffn_swiglu(w.x, w.ffn, ws=ws),
+        "moe_ffn": lambda: aflex.moe_ffn(x, moe, logits, 2, ws=ws),
+        "linear": lambda: aflex.linear(x, x, ws=ws),
+        "moe_block": lambda: aflex.moe_block(x, moe, x[0], x, 2, ws=ws),
+    }[op]
+    with pytest.raises(ValueError, match="cuda device"):
+        call()
+    assert calls == []
