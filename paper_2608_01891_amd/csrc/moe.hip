@@ -9,8 +9,9 @@
 //      prefix, the stable (expert, token, slot) order of the token/slot pairs,
 //      each pair's position in that order, and the m-tile map of the grouped
 //      GEMMs. One work-group up to 512 tokens, else two kernels over chunks of
-//      64 tokens; ranks count the expert's earlier tokens in bit masks, so the
-//      order is deterministic (and the same for both paths).
+//      64 tokens (and a scan of the chunks' counts between them where there are
+//      very many); ranks count the expert's earlier tokens in bit masks, so the
+//      order is deterministic (and the same for all paths).
 //   2. grouped gate/up GEMM with fused SwiGLU; the A rows are gathered from x
 //      through the pair order (no permuted copy of x is written).
 //   3. grouped down GEMM into fp32 split-K partials, rows in pair order.
@@ -29,6 +30,8 @@ constexpr int kMaxE = 64;
 // larger batches take two kernels over chunks of kChunk tokens.
 constexpr int kSingleRouteMaxT = 512;
 constexpr int kChunk = 64;
+// Chunks above which a launch between the two adds up the chunks' counts.
+constexpr int kMaxSummedChunks = 512;
 
 // Workspace: a routing block (ids .. num_tiles, written by the route kernel)
 // followed by the expert block (h, P). The two can live apart: the pipeline
@@ -74,7 +77,7 @@ static MoeLayout moe_layout(const aflex_ffn_args& f) {
   L.pos = take(pairs * 4);
   L.tile_map = take((size_t)L.max_tiles * 3 * 4);
   L.num_tiles = take(4);
-  L.blockcnt = take(((size_t)f.T + kChunk - 1) / kChunk * f.E * 4);
+  L.blockcnt = take((((size_t)f.T + kChunk - 1) / kChunk + 1) * f.E * 4);  // (and a row of totals)
   L.route_total = o;
   o = 0;
   L.h = take(pairs * f.I * 2);
@@ -390,12 +393,48 @@ __global__ __launch_bounds__(8 * kChunk) void moe_topk_kernel(const float* __res
   }
 }
 
+// Chunk counts of one expert per work-group into what the earlier chunks hold,
+// and the total into the row past the last chunk. For more than kMaxSummedChunks
+// chunks: every placing work-group reading all counts grows with the square of
+// the chunks (all of the routing, E = 8, k = 2: 512 chunks 17 us either way, 1024
+// 25 -> 18, 2048 65 -> 27, 8192 718 -> 75).
+__global__ __launch_bounds__(1024) void moe_scan_kernel(int32_t* blockcnt, int nblk, int E) {
+  __shared__ int wsum[16];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  int32_t* col = blockcnt + blockIdx.x;
+  int base = 0;
+  for (int b0 = 0; b0 < nblk; b0 += 1024) {
+    const int b = b0 + tid;
+    const int v = b < nblk ? col[(size_t)b * E] : 0;
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    int before = base, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      before += w < wave ? wsum[w] : 0;
+      all += wsum[w];
+    }
+    if (b < nblk) col[(size_t)b * E] = before + incl - v;
+    base += all;
+    __syncthreads();  // (wsum is written again)
+  }
+  if (tid == 0) col[(size_t)nblk * E] = base;
+}
+
 // Places a chunk's pairs: every work-group adds up all chunks' counts (8 groups
-// of 64 lanes, lane e for expert e), the first one writes offsets and tile map.
-// `pos` holds the ranks within the chunk on entry.
+// of 64 lanes, lane e for expert e) or, with `scanned`, reads the sums of
+// moe_scan_kernel; the first one writes offsets and tile map. `pos` holds the
+// ranks within the chunk on entry.
 __global__ __launch_bounds__(8 * kChunk) void moe_place_kernel(const int32_t* __restrict__ ids,
-                                                               const int32_t* __restrict__ blockcnt, int nblk, int T,
-                                                               int E, int k, int bm, int32_t* offsets,
+                                                               const int32_t* __restrict__ blockcnt, int nblk,
+                                                               bool scanned, int T, int E, int k, int bm,
+                                                               int32_t* offsets,
                                                                int32_t* u_offsets, int32_t* tile_map,
                                                                int32_t* num_tiles, int32_t* sorted, int32_t* pos,
                                                                int32_t* u_sorted) {
@@ -407,7 +446,12 @@ __global__ __launch_bounds__(8 * kChunk) void moe_place_kernel(const int32_t* __
   const size_t i = (size_t)blk * kChunk * k + tid;
   const int e = tid < n ? ids[i] : 0, r = tid < n ? pos[i] : 0;
   int tot = 0, pre = 0;
-  if (lane < E) {
+  if (scanned) {
+    if (part == 0 && lane < E) {
+      tot = blockcnt[(size_t)nblk * E + lane];
+      pre = blockcnt[(size_t)blk * E + lane];
+    }
+  } else if (lane < E) {
 #pragma unroll 4
     for (int b = part; b < nblk; b += kParts) {
       const int v = blockcnt[(size_t)b * E + lane];
@@ -533,7 +577,9 @@ hipError_t launch_moe_route(const aflex_ffn_args& f, void* route_ws, hipStream_t
   int32_t* blockcnt = reinterpret_cast<int32_t*>(w + L.blockcnt);
   moe_topk_kernel<<<nblk, 8 * kChunk, 0, stream>>>(f.router_logits, f.T, f.E, f.k, ids, wts, f.topk_ids, f.topk_w,
                                                    blockcnt, pos);
-  moe_place_kernel<<<nblk, 8 * kChunk, 0, stream>>>(ids, blockcnt, nblk, f.T, f.E, f.k, L.bm, offsets,
+  const bool scan = nblk > kMaxSummedChunks;
+  if (scan) moe_scan_kernel<<<f.E, 1024, 0, stream>>>(blockcnt, nblk, f.E);
+  moe_place_kernel<<<nblk, 8 * kChunk, 0, stream>>>(ids, blockcnt, nblk, scan, f.T, f.E, f.k, L.bm, offsets,
                                                     f.expert_offsets, tile_map, num_tiles, sorted, pos,
                                                     f.sorted_pairs);
   return hipGetLastError();

@@ -33,3 +33,10 @@ def test_routing_exact(gpu_lib, T, E, k):
     assert np.array_equal(r["sorted_pairs"].cpu().numpy(), order)
     counts = np.bincount(flat, minlength=E)
     assert np.array_equal(r["expert_offsets"].cpu().numpy(), np.concatenate([[0], np.cumsum(counts)]))
+
+
+# the last count of chunks that every work-group adds up, the first that is scanned,
+# and more chunks than the scan takes at a time
+@pytest.mark.parametrize("T,E,k", [(32768, 8, 2), (32769, 8, 2), (32769, 64, 8), (65601, 9, 1), (65601, 17, 3)])
+def test_routing_exact_many_chunks(gpu_lib, T, E, k):
+    test_routing_exact(gpu_lib, T, E, k)
