@@ -91,13 +91,25 @@ inline void plan_splits(int base_tiles, int K, int target, int slots, int min_st
   *kps = steps * 64;
 }
 
-// Weights up to this size stay in the 256 MB Infinity Cache for a next call with
-// them (the other microbatches of a layer, a small model), so their loads are
-// ordinary; larger ones, where each byte is read by one work-group, load
-// non-temporally. Linear of 8192 x 5120 (84 MB), called again and again, T = 64:
-// 28.4 us non-temporal, 23.7 ordinary; SwiGLU of 5120 x 25600 (786 MB), T = 200:
-// 201 and 211.
+// Weights up to this size load ordinarily, larger ones, where each byte is read
+// by one work-group, non-temporally. The small ones may still be in the 256 MB
+// Infinity Cache when a next call needs them (the other microbatches of a layer, a
+// small model), and lose nothing where they are not. Times in us, ordinary and
+// non-temporal loads, with the weights rotated through 1.3 GB and repeated:
+//                                    rotated        repeated
+//   linear 8192 x 5120 (84 MB), T = 64   26.6  28.6   22.4  28.5
+//   linear 8192 x 5120, T = 32           23.6  24.3   19.4  23.2
+//   SwiGLU 2816 x 9216 (156 MB), T = 64  51.3  53.6   39.0  53.5
+//   SwiGLU 4096 x 14336 (352 MB), T = 32 76.2  74.1   83.8  82.0
 constexpr long long kKeepWeightBytes = 160ll << 20;
+// The same line up to 16 tokens, and for the experts of a MoE call, where rotated
+// weights stream faster non-temporally from smaller sizes on:
+//   linear 5120 x 5120 (52 MB), T = 8    17.4  17.2   13.9  15.4
+//   linear 8192 x 5120 (84 MB), T = 8    21.7  20.7   17.9  18.9
+//   SwiGLU 2048 x 4096 (50 MB), T = 8    24.2  24.3   19.7  22.8
+//   MoE E = 8, 2048 x 768 (75 MB), T = 24    33.5  32.9   27.2  31.8
+//   MoE E = 8, 1024 x 2816 (138 MB), T = 24  43.6  41.3   34.3  39.8
+constexpr long long kKeepFewRowsBytes = 48ll << 20;
 
 // Work-groups of a GEMM below which smaller tiles, of which there are more, are
 // faster although they read more (256 CUs). SwiGLU 4096 x 14336, 128-row tiles
@@ -105,11 +117,34 @@ constexpr long long kKeepWeightBytes = 160ll << 20;
 // tiles: T = 256 145 and 124 us. 5120 x 25600 (200 work-groups): T = 40 143 and
 // 157 us; 2048 x 22400 (175): T = 200 91 and 113 us.
 constexpr int kFewWorkGroups = 160;
-// The same for MoE calls, whose tile count is an estimate: few enough that tiles
-// of half the height still fit one round. E = 8, 512 x 512, k = 2, T = 1000: 55 ->
-// 32 us with 64-row tiles; E = 4, 1024 x 1024, T = 300: 56 -> 31; but with 144
-// work-groups (E = 3, 4096 x 3008, T = 600) 128-row tiles 178, 256-row tiles 129 us.
+// The same for MoE calls, whose tile count is an estimate (every expert the
+// average): so few that tiles of half the height still fit one round when the
+// estimate is off. E = 8, 512 x 512, k = 2, T = 1000: 55 -> 32 us with 64-row
+// tiles; E = 4, 1024 x 1024, T = 300: 56 -> 31; but with 144 work-groups (E = 3,
+// 4096 x 3008, T = 600) 128-row tiles 178, 256-row tiles 129 us.
 constexpr int kFewGroupedWorkGroups = 112;
+
+// Tiles of a MoE call. `once`: experts' rows are expected to fit one tile (average
+// rows per expert x 1.3 <= bm, the margin pick_bm uses for 32-row tiles; always at
+// 32 rows), so each expert's weights are streamed once and, where they are more
+// than stays cached, load non-temporally (4-5% faster at 32-48 rows per expert on
+// 64-row tiles, 11% at 64 on 128-row tiles, 5-6% at 112-190 on 256-row tiles:
+// T = 509 580 -> 550 us).
+struct MoePlan {
+  int bm;  // rows per m-tile: 32, 64, 128 or 256
+  bool once, nt;
+};
+
+inline MoePlan plan_moe(long long pairs, int H, int I, int E) {
+  MoePlan pl;
+  pl.bm = pick_bm((double)pairs / E);
+  const long long avg = (pairs + E - 1) / E;
+  auto work_groups = [&](int bm) { return E * ((avg + bm - 1) / bm) * ((I + gate_bn(bm) - 1) / gate_bn(bm)); };
+  while (pl.bm > 64 && work_groups(pl.bm) <= kFewGroupedWorkGroups) pl.bm /= 2;
+  pl.once = pl.bm == 32 || (double)pairs / E * 1.3 <= (double)pl.bm;
+  pl.nt = pl.once && 6ll * E * H * I > kKeepFewRowsBytes;
+  return pl;
+}
 
 // Plan of a linear layer [N, K] (gate_cols = 0) or of a SwiGLU whose down matrix
 // is [N, K] and whose gate and up matrices are [gate_cols, N]: the largest tile
@@ -120,7 +155,7 @@ constexpr int kFewGroupedWorkGroups = 112;
 // tiles, 108 with 64). Small matrices gain most: SwiGLU 512 x 1408, T = 700 46 ->
 // 21 us, linear 2048 x 1024, T = 200 20.5 -> 11.3.
 inline FfnPlan plan_dense(int T, int N, int K, int gate_cols) {
-  const bool keep = (gate_cols ? 3ll : 1ll) * N * K * 2 <= kKeepWeightBytes;
+  const bool keep = (gate_cols ? 3ll : 1ll) * N * K * 2 <= (T <= 16 ? kKeepFewRowsBytes : kKeepWeightBytes);
   FfnPlan pl;
   auto try_bm = [&](int bm) {  // returns the work-groups of the first GEMM
     const int mtiles = (T + bm - 1) / bm;

@@ -40,24 +40,16 @@ struct MoeLayout {
   size_t ids, wts, offsets, sorted, pos, tile_map, num_tiles, blockcnt, route_total;
   size_t h, P, expert_total;
   int bm, max_tiles, down_splits, down_kps;
-  // Experts' rows are expected to fit one tile (average rows per expert x 1.3
-  // <= bm, the margin pick_bm uses for 32-row tiles; always at 32 rows), so each
-  // expert's weights are streamed once and, where they are more than stays
-  // cached, load non-temporally (4-5% faster at 32-48 rows per expert on 64-row
-  // tiles, 11% at 64 on 128-row tiles, 5-6% at 112-190 on 256-row tiles: T = 509
-  // 580 -> 550 us).
   bool once, nt;
 };
 
 static MoeLayout moe_layout(const aflex_ffn_args& f) {
   MoeLayout L;
   const size_t pairs = (size_t)f.T * f.k;
-  L.bm = pick_bm((double)pairs / f.E);
-  const long long avg = ((long long)pairs + f.E - 1) / f.E;  // rows per expert
-  auto work_groups = [&](int bm) { return f.E * ((avg + bm - 1) / bm) * ((f.I + gate_bn(bm) - 1) / gate_bn(bm)); };
-  while (L.bm > 64 && work_groups(L.bm) <= kFewGroupedWorkGroups) L.bm /= 2;
-  L.once = L.bm == 32 || (double)pairs / f.E * 1.3 <= (double)L.bm;
-  L.nt = L.once && 6ll * f.E * f.H * f.I > kKeepWeightBytes;
+  const MoePlan pl = plan_moe((long long)pairs, f.H, f.I, f.E);
+  L.bm = pl.bm;
+  L.once = pl.once;
+  L.nt = pl.nt;
   L.max_tiles = (int)((pairs + L.bm - 1) / L.bm) + f.E;
   const int ntiles = (f.H + down_bn(L.bm) - 1) / down_bn(L.bm);
   // The tile count is a worst case here (the routing stays on the device):

@@ -1,0 +1,69 @@
+"""GEMM tile plans on the host: the rules of csrc/ffn_plan.h, compiled for the
+host alone, at the shapes that stand for each side of a line."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2608_01891_amd import build
+
+MAIN = r"""
+#include <stdio.h>
+#include <string.h>
+#include "ffn_plan.h"
+int main() {
+  char op[16];
+  int a, b, c, d;
+  while (scanf("%15s %d %d %d %d", op, &a, &b, &c, &d) == 5) {
+    if (!strcmp(op, "moe")) {  // pairs H I E
+      const aflex::MoePlan p = aflex::plan_moe(a, b, c, d);
+      printf("%d %d 0 0\n", p.bm, p.nt);
+    } else {  // T N K gate_cols
+      const aflex::FfnPlan p = aflex::plan_dense(a, b, c, d);
+      printf("%d %d %d %d\n", p.bm, p.nt, p.down_splits, p.down_kps);
+    }
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    """Plans of many calls at once: [(rows per tile, non-temporal, K splits, k per split)]."""
+    d = tmp_path_factory.mktemp("plan")
+    src, exe = d / "main.hip", d / "main"
+    src.write_text(MAIN)
+    cmd = [build.HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17", f"-I{build.CSRC}",
+           f"-I{build.INCLUDE}", str(src), "-o", str(exe)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def ask(calls):
+        text = "".join(" ".join(map(str, c)) + "\n" for c in calls)
+        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
+        return [tuple(map(int, line.split())) for line in out.splitlines()]
+
+    return ask
+
+
+def linear(T, K, N):
+    return ("dense", T, N, K, 0)
+
+
+def swiglu(T, H, I):
+    return ("dense", T, H, I, I)
+
+
+def moe(T, H, I, E, k):
+    return ("moe", T * k, H, I, E)
+
+
+# calls whose weights come from memory each time (a deep model's) must not lose to keeping them cached
+@pytest.mark.parametrize("call,nt", [
+    (linear(8, 5120, 5120), 1), (linear(8, 5120, 4096), 0), (linear(16, 8192, 5120), 1), (linear(17, 8192, 5120), 0),
+    (linear(64, 8192, 5120), 0), (linear(32, 8192, 10304), 1), (linear(64, 8192, 10304), 1),
+    (swiglu(16, 2048, 4096), 0), (swiglu(16, 2048, 5632), 1), (swiglu(32, 2048, 5632), 0), (swiglu(32, 4096, 14336), 1),
+    (moe(24, 2048, 512, 8, 2), 0), (moe(24, 2048, 768, 8, 2), 1), (moe(128, 1024, 2816, 8, 2), 1),
+    (moe(24, 512, 768, 64, 8), 1), (moe(2048, 1024, 2816, 8, 2), 0)])
+def test_non_temporal_weights(plans, call, nt):
+    assert plans([call])[0][1] == nt
