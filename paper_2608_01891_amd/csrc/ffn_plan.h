@@ -146,16 +146,34 @@ inline MoePlan plan_moe(long long pairs, int H, int I, int E) {
   return pl;
 }
 
+// Weights of a linear layer up to which 33 ... 128 tokens take 64-row tiles (two
+// work-groups per CU) although 128-row tiles fill the chip too. 64- and 128-row
+// tiles, weights rotated through 1.3 GB and repeated: 8192 x 4096 (67 MB), T = 80
+// 24.0 24.9 and 20.0 22.9 us, T = 128 29.1 27.8 and 22.3 26.0; 8192 x 5632 (92 MB),
+// T = 80 34.8 29.5 and 32.0 26.1; 5120 x 10240 (105 MB), T = 48 30.2 28.4 and 23.8
+// 24.3, T = 128 39.7 34.7 and 28.5 30.5.
+constexpr long long kSmallTileBytes = 84ll << 20;
+
 // Plan of a linear layer [N, K] (gate_cols = 0) or of a SwiGLU whose down matrix
 // is [N, K] and whose gate and up matrices are [gate_cols, N]: the largest tile
 // of 256, 128 or 64 rows whose first GEMM has enough work-groups, unless the next
-// smaller takes a second round of them; 32 rows up to 32 tokens. Up to 128 tokens, weights that stay cached take 64-row tiles, two
-// work-groups per CU (linear 8192 x 5120, T = 128: 28.5 -> 25.1 us); larger ones
-// only where one tile holds all rows (4096 x 14336, T = 128: 105 us with 128-row
-// tiles, 108 with 64). Small matrices gain most: SwiGLU 512 x 1408, T = 700 46 ->
-// 21 us, linear 2048 x 1024, T = 200 20.5 -> 11.3.
+// smaller takes a second round of them; 32 rows up to 32 tokens. Small matrices
+// gain most: SwiGLU 512 x 1408, T = 700 46 -> 21 us, linear 2048 x 1024, T = 200
+// 20.5 -> 11.3.
+//
+// Up to 64 tokens, where one 64-row tile holds all rows, weights that stay cached
+// take it, unless a linear layer's work-groups are a few more than the CUs, some
+// of which then hold two (4096 x 5120, T = 40, 320 work-groups of 64 rows or 160
+// of 128: 18.0 and 17.3 us; 4096 x 4096, 256 or 128: 13.5 and 16.4). From 65 on
+// two 64-row tiles read every weight twice, which pays only where the 128-row
+// tiles leave CUs idle (SwiGLU 2048 x 8192, T = 128, 64 work-groups of 128 rows:
+// 43.0 us with 64-row tiles, 57.1 with 128; 1024 x 25600, 200 work-groups: 68.0
+// and 55.4) or, in a small linear layer, the 64-row tiles fill one round of the
+// chip (2048 x 16384, T = 80: 24.2 and 25.0; 4096 x 11264, two rounds: 39.2 and
+// 28.2). (Weights rotated through 1.3 GB.)
 inline FfnPlan plan_dense(int T, int N, int K, int gate_cols) {
-  const bool keep = (gate_cols ? 3ll : 1ll) * N * K * 2 <= (T <= 16 ? kKeepFewRowsBytes : kKeepWeightBytes);
+  const long long bytes = (gate_cols ? 3ll : 1ll) * N * K * 2;
+  const bool keep = bytes <= (T <= 16 ? kKeepFewRowsBytes : kKeepWeightBytes);
   FfnPlan pl;
   auto try_bm = [&](int bm) {  // returns the work-groups of the first GEMM
     const int mtiles = (T + bm - 1) / bm;
@@ -163,6 +181,9 @@ inline FfnPlan plan_dense(int T, int N, int K, int gate_cols) {
     pl.bm = bm;
     plan_splits(mtiles * ntiles, K, down_target(bm), concurrent_wgs(bm), 8, &pl.down_splits, &pl.down_kps);
     return (long long)mtiles * (gate_cols ? (gate_cols + gate_bn(bm) - 1) / gate_bn(bm) : ntiles * pl.down_splits);
+  };
+  auto one_round = [&](int bm, long long n) {  // of resident work-groups, nearly full
+    return n <= concurrent_wgs(bm) && n * 16 >= concurrent_wgs(bm) * 15ll;
   };
   if (T <= 32) {
     try_bm(32);
@@ -174,8 +195,17 @@ inline FfnPlan plan_dense(int T, int N, int K, int gate_cols) {
       else if (n128 <= kFewWorkGroups && try_bm(64) > concurrent_wgs(64))
         try_bm(128);
     }
-  } else if (keep || (try_bm(128) <= kFewWorkGroups && T <= 64)) {
-    try_bm(64);
+  } else {
+    const long long n64 = try_bm(64), n128 = try_bm(128);
+    const bool few = n128 <= kFewWorkGroups;
+    bool small;
+    if (T <= 64 && gate_cols)
+      small = few || keep;
+    else if (T <= 64)
+      small = n64 <= 256 || (n64 >= 384 && bytes <= kSmallTileBytes);
+    else
+      small = keep && (few || (!gate_cols && bytes <= kSmallTileBytes && (one_round(64, n64) || !one_round(128, n128))));
+    if (small) try_bm(64);
   }
   pl.nt = !keep && T <= pl.bm;
   return pl;

@@ -67,3 +67,16 @@ def moe(T, H, I, E, k):
     (moe(24, 512, 768, 64, 8), 1), (moe(2048, 1024, 2816, 8, 2), 0)])
 def test_non_temporal_weights(plans, call, nt):
     assert plans([call])[0][1] == nt
+
+
+# 33 ... 128 tokens: one 64-row tile, or two that read the weights twice, against one of 128 rows
+@pytest.mark.parametrize("call,bm", [
+    (linear(33, 8192, 5120), 64), (linear(64, 8192, 5120), 64), (linear(128, 8192, 5120), 64),
+    (linear(64, 5120, 10240), 128), (linear(96, 7168, 9216), 128), (linear(128, 4096, 11264), 128),
+    (linear(80, 4096, 9216), 128),
+    (linear(40, 4096, 5120), 128), (linear(72, 4096, 5120), 64), (linear(40, 4096, 4096), 64), (linear(40, 5120, 5120), 64), (linear(128, 2048, 16384), 64), (linear(128, 2048, 1024), 64),
+    (linear(64, 8192, 10304), 128), (linear(128, 8192, 10304), 128),
+    (swiglu(64, 1024, 25600), 64), (swiglu(65, 1024, 25600), 128), (swiglu(128, 2048, 8192), 64),
+    (swiglu(64, 4096, 14336), 64), (swiglu(65, 4096, 14336), 128), (swiglu(33, 5120, 25600), 128)])
+def test_rows_up_to_128_tokens(plans, call, bm):
+    assert plans([call])[0][0] == bm
