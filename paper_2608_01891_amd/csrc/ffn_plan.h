@@ -154,6 +154,14 @@ inline MoePlan plan_moe(long long pairs, int H, int I, int E) {
 // 24.3, T = 128 39.7 34.7 and 28.5 30.5.
 constexpr long long kSmallTileBytes = 84ll << 20;
 
+// k-steps per split up to which a linear layer's 256-row tiles are worse than
+// 128-row ones that fill one round of the chip too: those take half the splits of
+// twice the length, so half the fp32 partials and fewer of the loops' beginnings
+// and ends (256- and 128-row tiles: 4096 x 4096, T = 512, 8 and 16 steps 45.4 and
+// 32.8 us, T = 1024, 16 and 32 steps 55.1 and 47.7; 5120 x 5120, T = 512, 14 steps
+// 45.9 and 42.6; 8192 x 5120, T = 320, 22 steps 42.6 and 44.2).
+constexpr int kFewSteps = 16;
+
 // Plan of a linear layer [N, K] (gate_cols = 0) or of a SwiGLU whose down matrix
 // is [N, K] and whose gate and up matrices are [gate_cols, N]: the largest tile
 // of 256, 128 or 64 rows whose first GEMM has enough work-groups, unless the next
@@ -194,6 +202,8 @@ inline FfnPlan plan_dense(int T, int N, int K, int gate_cols) {
         try_bm(256);
       else if (n128 <= kFewWorkGroups && try_bm(64) > concurrent_wgs(64))
         try_bm(128);
+    } else if (!gate_cols && pl.down_kps <= kFewSteps * 64 && !one_round(128, try_bm(128))) {
+      try_bm(256);
     }
   } else {
     const long long n64 = try_bm(64), n128 = try_bm(128);
