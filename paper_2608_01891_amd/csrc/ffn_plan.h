@@ -155,11 +155,13 @@ inline MoePlan plan_moe(long long pairs, int H, int I, int E) {
 constexpr long long kSmallTileBytes = 84ll << 20;
 
 // k-steps per split up to which a linear layer's 256-row tiles are worse than
-// 128-row ones that fill one round of the chip too: those take half the splits of
-// twice the length, so half the fp32 partials and fewer of the loops' beginnings
-// and ends (256- and 128-row tiles: 4096 x 4096, T = 512, 8 and 16 steps 45.4 and
-// 32.8 us, T = 1024, 16 and 32 steps 55.1 and 47.7; 5120 x 5120, T = 512, 14 steps
-// 45.9 and 42.6; 8192 x 5120, T = 320, 22 steps 42.6 and 44.2).
+// 128-row ones that fill one round of the chip too, or are as many: those take
+// half the splits of twice the length, so half the fp32 partials and fewer of the
+// loops' beginnings and ends (256- and 128-row tiles: 4096 x 4096, T = 512, 8 and
+// 16 steps 45.4 and 32.8 us, T = 1024, 16 and 32 steps 55.1 and 47.7; 5120 x 5120,
+// T = 512, 14 steps 45.9 and 42.6; 8192 x 5120, T = 320, 22 steps 42.6 and 44.2;
+// 2048 x 4096, 192 work-groups of either, T = 768, 4 and 2 splits 36.1 and 28.2,
+// T = 1536, 2 splits and 1 45.2 and 65.9).
 constexpr int kFewSteps = 16;
 
 // Plan of a linear layer [N, K] (gate_cols = 0) or of a SwiGLU whose down matrix
@@ -196,14 +198,16 @@ inline FfnPlan plan_dense(int T, int N, int K, int gate_cols) {
   if (T <= 32) {
     try_bm(32);
   } else if (T > 128) {
-    if (try_bm(256) <= kFewWorkGroups) {
+    const long long n256 = try_bm(256);
+    if (n256 <= kFewWorkGroups) {
       const long long n128 = try_bm(128);
       if (n128 > concurrent_wgs(128))
         try_bm(256);
       else if (n128 <= kFewWorkGroups && try_bm(64) > concurrent_wgs(64))
         try_bm(128);
-    } else if (!gate_cols && pl.down_kps <= kFewSteps * 64 && !one_round(128, try_bm(128))) {
-      try_bm(256);
+    } else if (!gate_cols && pl.down_kps <= kFewSteps * 64) {
+      const long long n128 = try_bm(128);
+      if (!one_round(128, n128) && (n128 < n256 || n128 > concurrent_wgs(128) || pl.down_splits == 1)) try_bm(256);
     }
   } else {
     const long long n64 = try_bm(64), n128 = try_bm(128);

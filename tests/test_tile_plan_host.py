@@ -86,7 +86,7 @@ def test_rows_up_to_128_tokens(plans, call, bm):
 @pytest.mark.parametrize("call,bm", [
     (linear(512, 4096, 4096), 128), (linear(768, 4096, 4096), 256), (linear(1024, 4096, 4096), 128),
     (linear(256, 5120, 5120), 128), (linear(640, 5120, 5120), 256), (linear(256, 8192, 5120), 128),
-    (linear(320, 8192, 5120), 256), (linear(1536, 2048, 4096), 256), (linear(4096, 4096, 4096), 256),
+    (linear(320, 8192, 5120), 256), (linear(768, 2048, 4096), 128), (linear(1536, 2048, 4096), 256), (linear(4096, 4096, 4096), 256),
     (swiglu(512, 4096, 14336), 256)])
 def test_few_k_steps(plans, call, bm):
     assert plans([call])[0][0] == bm
