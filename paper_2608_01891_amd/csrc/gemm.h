@@ -8,7 +8,7 @@
 // ring of 2-4 LDS stages (global_load_lds_dwordx4, no register staging), so
 // the loads of the next k-steps are in flight while kt is multiplied
 // (v_mfma_f32_16x16x32_bf16 for the 32/64-row tiles, v_mfma_f32_32x32x16_bf16
-// for the 128/256-row ones). At decode batch sizes these GEMMs stream
+// for the 128-row ones; 256-row tiles are gemm_ring.h). At decode batch sizes these GEMMs stream
 // weights, so the depth of the load pipeline, not the MFMA rate, sets their
 // speed.
 //
@@ -24,8 +24,8 @@
 // are dispatched round-robin over the 8 XCDs; the logical tile index is
 // remapped so that consecutive tiles (which share an A tile, or for dense
 // GEMMs a weight tile across m-tiles) land on the same XCD and its L2. With a
-// device-side tile map the remap can run over the real tile count instead of
-// the grid (mt_major = 2), so the tiles spread evenly over the XCDs.
+// device-side tile map the remap runs over the real tile count instead of the
+// grid, so the tiles spread evenly over the XCDs.
 // m-tiles come either from a dense row count or from a device-side tile map
 // of (expert, first row, end row) triples written by the MoE routing kernel;
 // work-groups beyond the map's device-side count exit at once, so the grid is
@@ -56,8 +56,7 @@ struct GemmParams {
   const int32_t* num_mtiles;  // device count of valid tile_map entries
   int max_mtiles;
   int n_ntiles;
-  int mt_major;               // 1: m-tile is the slow index of the tile order; 2: the same over
-                              // the device-side row-tile count (tile_map only), spread over the XCDs
+  int mt_major;               // 1: m-tile is the slow index of the tile order
   uint16_t* C;                // bf16 output [rows, ldc]
   int ldc;
   const uint16_t* R;          // optional bf16 residual [rows, ldc] added before rounding (plain bf16 output only)
@@ -149,11 +148,14 @@ struct GemmTile {
 __device__ __forceinline__ bool gemm_tile_of(const GemmParams& p, GemmTile& x) {
   int t, splits = p.splits, mrange = p.max_mtiles;
   x.kps = p.k_per_split;
-  if (p.mt_major == 2 || p.split_slots > 0) {
-    // Row tiles from the device-side count (and the split count planned from
-    // it): the real tiles spread evenly over the XCDs. Expert-major
-    // (mt_major = 2), each XCD takes consecutive n-tiles of one or two experts,
-    // whose token rows then stay in its L2.
+  if (p.tile_map) {
+    // Row tiles from the device-side count (and with split_slots the split count
+    // planned from it): the real tiles are the first work-groups, spread evenly
+    // over the XCDs. (Spread over the grid with the empty ones between them, a CU
+    // got two while others had none: E = 10, k = 2, 2048 x 2688, T = 1175, 210 tiles
+    // of 420, gate/up 98 us instead of 57.) Expert-major (mt_major), each XCD
+    // takes consecutive n-tiles of one or two experts, whose token rows then stay
+    // in its L2.
     const int mtiles = *p.num_mtiles;
     if (p.split_slots > 0) split_plan_slots(mtiles * p.n_ntiles, p.K / 64, p.splits, p.split_slots, &splits, &x.kps);
     const int nreal = mtiles * p.n_ntiles * splits;
@@ -183,7 +185,6 @@ __device__ __forceinline__ bool gemm_tile_of(const GemmParams& p, GemmTile& x) {
   }
   x.expert = 0;
   if (p.tile_map) {
-    if (mt >= *p.num_mtiles) return false;
     x.expert = p.tile_map[3 * mt + 0];
     x.row0 = p.tile_map[3 * mt + 1];
     x.row1 = p.tile_map[3 * mt + 2];

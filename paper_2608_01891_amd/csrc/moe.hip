@@ -622,7 +622,7 @@ hipError_t launch_moe_experts(const aflex_ffn_args& f, void* route_ws, void* exp
   // us). Otherwise an expert's m-tiles stay adjacent, so its overflow tiles
   // re-read the weights from L2 (the expert-major order took 512 tokens from
   // 745 to 820 us).
-  const int order = L.once ? 2 : 0;
+  const int order = L.once;
   g.mt_major = order;
   g.C = h;
   g.ldc = f.I;

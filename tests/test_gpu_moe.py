@@ -185,3 +185,18 @@ def test_many_down_splits(gpu_lib, T, H, I, E, k):
     _check_routing(r, logits, k, E)
     ref, _, _ = oracle.moe_ffn(x, logits, w.w_gate, w.w_up, w.w_down, k)
     check_rows(y.cpu(), ref, what=f"moe many splits T={T} I={I} k={k}")
+
+
+@pytest.mark.parametrize("T,H,I,E,k", [(300, 64, 192, 64, 1),    # 32-row tiles, expert by expert
+                                       (400, 128, 192, 8, 2),    # 64-row tiles, two per expert
+                                       (470, 64, 2752, 10, 2)])  # 128-row tiles, one per expert
+def test_few_of_many_possible_tiles(gpu_lib, T, H, I, E, k):
+    """All tokens on the last k experts: of the row tiles that the grid allows for
+    only a few exist, and the work-groups past them must leave every output to
+    the others, in both tile orders."""
+    x, w, logits = synth.custom_ffn(95 + T, T, H, I, E=E)
+    logits[:, E - k:] += 50.0
+    y, r = aflex.moe_ffn(x.to(DEV), w.to(DEV), logits.to(DEV), k, routing=True)
+    _check_routing(r, logits, k, E)
+    ref, _, _ = oracle.moe_ffn(x, logits, w.w_gate, w.w_up, w.w_down, k)
+    check_rows(y.cpu(), ref, what=f"few of many tiles T={T} E={E}")
