@@ -1,22 +1,23 @@
 // Tile and split-K planning shared by the dense and MoE FFN launchers.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 
 #include "gemm.h"
 
 namespace aflex {
 
-// Output columns per gate/up tile (x2 weight rows) and per down tile. The
-// 128- and 256-row tiles take a CU's whole LDS (one work-group per CU).
+// Output columns per gate/up tile (x2 weight rows) and per down tile. The tiles
+// of 128 rows and more take a CU's whole LDS (one work-group per CU).
 inline int gate_bn(int bm) { return bm >= 128 ? 128 : 64; }
 
 inline int down_bn(int bm) { return bm >= 128 ? 256 : 128; }
-// Work-groups the down GEMM's split-K aims for: the 256-row tiles run one
-// work-group per CU, so one round of the chip; smaller tiles two per CU.
+// Work-groups the down GEMM's split-K aims for: one round of the chip for the
+// tiles of one work-group per CU; smaller tiles run two per CU.
 constexpr int kOneWgPerCuTarget = 256;
 inline int down_target(int bm) { return bm >= 128 ? kOneWgPerCuTarget : (bm == 64 ? 2048 : 512); }
-// Work-groups resident on the 256 CUs at once: one per CU for the 128- and
-// 256-row tiles (the whole LDS), two for the smaller ones.
+// Work-groups resident on the 256 CUs at once: one per CU for the tiles of 128
+// rows and more (the whole LDS), two for the smaller ones.
 inline int concurrent_wgs(int bm) { return bm >= 128 ? 256 : 512; }
 
 struct FfnPlan {
@@ -51,7 +52,7 @@ inline int pick_bm(double rows_per_expert) {
 // filled blocks (Mixtral T = 2048, 472-541 rows per expert: 192 + 192 + 157
 // instead of 256 + 256 + 29); else bm.
 __host__ __device__ inline int tile_rows(int n, int bm) {
-  if (bm < 256 || n <= bm) return bm;
+  if (bm != 256 || n <= bm) return bm;
   const int tiles = (n + bm - 1) / bm, blocks = (n + 31) / 32;
   return (blocks + tiles - 1) / tiles * 32;
 }
@@ -131,17 +132,42 @@ constexpr int kFewGroupedWorkGroups = 112;
 // 64-row tiles, 11% at 64 on 128-row tiles, 5-6% at 112-190 on 256-row tiles:
 // T = 509 580 -> 550 us).
 struct MoePlan {
-  int bm;  // rows per m-tile: 32, 64, 128 or 256
+  int bm;  // rows per m-tile: 32, 64, 128, 256 or 320
   bool once, nt;
 };
 
-inline MoePlan plan_moe(long long pairs, int H, int I, int E) {
+// Row tiles of 256 that E experts are expected to take, their row counts spread
+// normally about the average.
+inline double expected_tiles256(int E, double avg, double sigma) {
+  double t = E;
+  for (int j = 1; 256.0 * j < avg + 6.0 * sigma + 1.0; ++j)
+    t += sigma > 0.0 ? E * 0.5 * erfc((256.0 * j - avg) / (sigma * sqrt(2.0))) : (avg > 256.0 * j ? E : 0);
+  return t;
+}
+
+// `k` experts per token. Where enough experts are expected to take one more
+// 256-row tile for the gate/up GEMM to need a second round of the chip, and
+// 320-row tiles (the eight-wave kernel, ten row blocks) hold them in one, those
+// are faster although their loop is not (256 rows -> 320): E = 8, k = 2, 1024 x
+// 3584, T = 1000 110.7 -> 101.9 us; 4096 x 3584, T = 1060 277 -> 259; E = 4, k = 2,
+// 3072 x 4096, T = 1120 223 -> 204. With rounds to spare they are not (E = 8, k = 2,
+// 4096 x 14336, T = 1000: 849 and 934), nor where the 256-row ones fit one (E = 8,
+// k = 2, 512 x 4096, T = 968: 77 and 81).
+inline MoePlan plan_moe(long long pairs, int H, int I, int E, int k) {
   MoePlan pl;
-  pl.bm = pick_bm((double)pairs / E);
+  const double rows = (double)pairs / E;
+  pl.bm = pick_bm(rows);
   const long long avg = (pairs + E - 1) / E;
   auto work_groups = [&](int bm) { return E * ((avg + bm - 1) / bm) * ((I + gate_bn(bm) - 1) / gate_bn(bm)); };
   while (pl.bm > 64 && work_groups(pl.bm) <= kFewGroupedWorkGroups) pl.bm /= 2;
-  pl.once = pl.bm == 32 || (double)pairs / E * 1.3 <= (double)pl.bm;
+  if (pl.bm == 256) {
+    const int ntiles = (I + gate_bn(256) - 1) / gate_bn(256), round = concurrent_wgs(256);
+    const double sigma = sqrt(rows * (1.0 - (double)k / E));  // tokens choose independently
+    if (floor(expected_tiles256(E, rows, sigma) + 0.5) * ntiles > round &&
+        E * ceil((rows + 3.0 * sigma) / 320.0) * ntiles <= round)
+      pl.bm = 320;
+  }
+  pl.once = pl.bm == 32 || (pl.bm != 320 && rows * 1.3 <= (double)pl.bm);
   pl.nt = pl.once && 6ll * E * H * I > kKeepFewRowsBytes;
   return pl;
 }

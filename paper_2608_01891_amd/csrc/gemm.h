@@ -8,7 +8,7 @@
 // ring of 2-4 LDS stages (global_load_lds_dwordx4, no register staging), so
 // the loads of the next k-steps are in flight while kt is multiplied
 // (v_mfma_f32_16x16x32_bf16 for the 32/64-row tiles, v_mfma_f32_32x32x16_bf16
-// for the 128-row ones; 256-row tiles are gemm_ring.h). At decode batch sizes these GEMMs stream
+// for the 128/320-row ones; 256-row tiles are gemm_ring.h). At decode batch sizes these GEMMs stream
 // weights, so the depth of the load pipeline, not the MFMA rate, sets their
 // speed.
 //
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(64 * WM * WN, LDS_BYTES > 81920 ? 1 : 2) void gemm_
     using I3 = std::integral_constant<int, 3 <= TM ? 3 : TM>;
     using I4 = std::integral_constant<int, 4 <= TM ? 4 : TM>;
     using IT = std::integral_constant<int, TM>;
-    static_assert(TM <= 4, "row blocks per wave");
+    static_assert(TM <= 5, "row blocks per wave");
     if (nact == 1)
       kloop(I1{});
     else if (nact == 2)

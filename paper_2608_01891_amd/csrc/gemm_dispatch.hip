@@ -6,7 +6,9 @@
 // columns of each gate/up matrix or 64 columns of the down matrix, one
 // work-group per CU in the whole 160 KiB of LDS as a ring of three stages); both
 // take 64-wide k-steps, so every k-step reads whole 128-byte lines of each row.
-// 256-row tiles are the MFMA-bound kernel of gemm_ring.h. Weights that one tile
+// 256-row tiles are the MFMA-bound kernel of gemm_ring.h; 320-row tiles, for MoE
+// calls that fit one round with them (plan_moe), the eight-wave shape with wave
+// tiles of 160 rows in two stages. Weights that one tile
 // streams exactly once load non-temporally where they are too large to stay
 // cached (128-row tiles, dense T = 128 of 786 MB: 188 -> 175 us).
 #include "ffn_plan.h"
@@ -34,6 +36,7 @@ hipError_t launch_gate_up(int bm, bool nt, const GemmParams& g, hipStream_t stre
       case 32: go<32, 64, 1, 4, 64, 16, true, false, 81920, NT>(g, grid, stream); break;
       case 64: go<64, 64, 2, 2, 64, 16, true, false, 81920, NT>(g, grid, stream); break;
       case 128: go<128, 128, 2, 4, 64, 32, true, false, 163840, NT>(g, grid, stream); break;
+      case 320: go<320, 128, 2, 4, 64, 32, true, false, 163840>(g, grid, stream); break;
       default: gemm_ring_kernel<true, false, NT><<<grid, 256, 0, stream>>>(g); break;
     }
   };
@@ -50,6 +53,7 @@ static void down(int bm, const GemmParams& g, unsigned grid, hipStream_t stream)
     case 32: go<32, 128, 1, 4, 64, 16, false, F32, 81920, NT>(g, grid, stream); break;
     case 64: go<64, 128, 2, 2, 64, 16, false, F32, 81920, NT>(g, grid, stream); break;
     case 128: go<128, 256, 2, 4, 64, 32, false, F32, 163840, NT>(g, grid, stream); break;
+    case 320: go<320, 256, 2, 4, 64, 32, false, F32, 163840>(g, grid, stream); break;
     default: gemm_ring_kernel<false, F32, NT><<<grid, 256, 0, stream>>>(g); break;
   }
 }

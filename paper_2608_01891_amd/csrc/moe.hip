@@ -46,7 +46,7 @@ struct MoeLayout {
 static MoeLayout moe_layout(const aflex_ffn_args& f) {
   MoeLayout L;
   const size_t pairs = (size_t)f.T * f.k;
-  const MoePlan pl = plan_moe((long long)pairs, f.H, f.I, f.E);
+  const MoePlan pl = plan_moe((long long)pairs, f.H, f.I, f.E, f.k);
   L.bm = pl.bm;
   L.once = pl.once;
   L.nt = pl.nt;

@@ -6,6 +6,7 @@ import functools
 import pytest
 import torch
 
+import oracle
 from paper_2608_01891_amd import aflex, synth
 from tests.parity import check_rows
 
@@ -68,3 +69,17 @@ def test_moe(gpu_lib, T, H, I):
         one = type("W", (), {"w_gate": w.w_gate[e], "w_up": w.w_up[e], "w_down": w.w_down[e]})
         ref[t] += p[t, j, None] * _swiglu64(x[t].double(), one)
     check_rows(y.cpu(), ref.cpu(), what=f"moe {T}x{H}x{I}")
+
+
+# 320-row tiles: experts of one tile and a few rows more, and of two tiles
+MOE_ONE_ROUND = [(1000, 128, 3584, 8, 2), (1100, 64, 3520, 8, 2), (1120, 128, 4096, 4, 2), (300, 64, 16384, 2, 2)]
+
+
+@pytest.mark.parametrize("T,H,I,E,k", MOE_ONE_ROUND)
+@pytest.mark.parametrize("skew", [0.0, 0.5])
+def test_moe_320_row_tiles(gpu_lib, T, H, I, E, k, skew):
+    x, w, logits = synth.custom_ffn(54, T, H, I, E=E)
+    logits[:, E - 1] += skew  # a crowded last expert: past its tile, or into a third one
+    y = aflex.moe_ffn(x.to(DEV), w.to(DEV), logits.to(DEV), k).cpu()
+    ref, _, _ = oracle.moe_ffn(x, logits, w.w_gate, w.w_up, w.w_down, k)
+    check_rows(y, ref, what=f"moe {T}x{H}x{I} E={E} k={k}")

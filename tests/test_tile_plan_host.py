@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 from paper_2608_01891_amd import build
+from tests import test_gpu_tile_plan
 
 MAIN = r"""
 #include <stdio.h>
@@ -13,12 +14,12 @@ MAIN = r"""
 #include "ffn_plan.h"
 int main() {
   char op[16];
-  int a, b, c, d;
-  while (scanf("%15s %d %d %d %d", op, &a, &b, &c, &d) == 5) {
-    if (!strcmp(op, "moe")) {  // pairs H I E
-      const aflex::MoePlan p = aflex::plan_moe(a, b, c, d);
+  int a, b, c, d, e;
+  while (scanf("%15s %d %d %d %d %d", op, &a, &b, &c, &d, &e) == 6) {
+    if (!strcmp(op, "moe")) {  // T H I E k
+      const aflex::MoePlan p = aflex::plan_moe((long long)a * e, b, c, d, e);
       printf("%d %d 0 0\n", p.bm, p.nt);
-    } else {  // T N K gate_cols
+    } else {  // T N K gate_cols 0
       const aflex::FfnPlan p = aflex::plan_dense(a, b, c, d);
       printf("%d %d %d %d\n", p.bm, p.nt, p.down_splits, p.down_kps);
     }
@@ -47,15 +48,15 @@ def plans(tmp_path_factory):
 
 
 def linear(T, K, N):
-    return ("dense", T, N, K, 0)
+    return ("dense", T, N, K, 0, 0)
 
 
 def swiglu(T, H, I):
-    return ("dense", T, H, I, I)
+    return ("dense", T, H, I, I, 0)
 
 
 def moe(T, H, I, E, k):
-    return ("moe", T * k, H, I, E)
+    return ("moe", T, H, I, E, k)
 
 
 # calls whose weights come from memory each time (a deep model's) must not lose to keeping them cached
@@ -89,4 +90,15 @@ def test_rows_up_to_128_tokens(plans, call, bm):
     (linear(320, 8192, 5120), 256), (linear(768, 2048, 4096), 128), (linear(1536, 2048, 4096), 256), (linear(4096, 4096, 4096), 256),
     (swiglu(512, 4096, 14336), 256)])
 def test_few_k_steps(plans, call, bm):
+    assert plans([call])[0][0] == bm
+
+
+# 320-row tiles: a second round of 256-row ones, or not; too many rows for them; rounds to spare
+@pytest.mark.parametrize("call,bm", [
+    (moe(1000, 1024, 3584, 8, 2), 320), (moe(940, 1024, 3584, 8, 2), 256), (moe(1240, 1024, 3584, 8, 2), 256),
+    (moe(1060, 4096, 3584, 8, 2), 320), (moe(1000, 512, 4096, 8, 2), 320), (moe(860, 512, 4096, 8, 2), 256),
+    (moe(1120, 3072, 4096, 4, 2), 320), (moe(960, 3072, 4096, 4, 2), 256), (moe(1220, 3072, 4096, 4, 2), 256),
+    (moe(1000, 4096, 14336, 8, 2), 256), (moe(2048, 4096, 14336, 8, 2), 256), (moe(1120, 2048, 2048, 8, 2), 256)]
+    + [(moe(*c), 320) for c in test_gpu_tile_plan.MOE_ONE_ROUND])
+def test_moe_one_round(plans, call, bm):
     assert plans([call])[0][0] == bm
