@@ -48,8 +48,10 @@ __device__ __forceinline__ uint32_t chunk_word(const uint4& v, int i) {
 // of the token-fastest tile when the block is entirely new (2-byte stores at a
 // partial first or last block). Bound by memory latency: all 16 rows of a block
 // are loaded before the first is stored (row by row, and K then V in one
-// thread, 9500 tokens of 8 heads x 128 took 30 us for 78 MB).
-template <bool XCHG>
+// thread, 9500 tokens of 8 heads x 128 took 30 us for 78 MB). FEW: fewer than 16
+// new tokens per sequence, so no block is whole, and only the rows a block has are
+// loaded.
+template <bool XCHG, bool FEW>
 __global__ __launch_bounds__(XCHG ? 256 : 1024) void kv_write_kernel(aflex_kv_write_args a) {
   const int chunks = a.D / 8;
   const int g = threadIdx.x / chunks, c = threadIdx.x % chunks;
@@ -76,12 +78,13 @@ __global__ __launch_bounds__(XCHG ? 256 : 1024) void kv_write_kernel(aflex_kv_wr
   uint4 row[16];
 #pragma unroll
   for (int o = 0; o < 16; ++o)  // (rows outside [o0, o1) repeat a row inside and are not stored)
-    row[o] = *reinterpret_cast<const uint4*>(src + (size_t)(shift + jb * 16 + min(max(o, o0), o1 - 1)) * row_stride);
+    if (!FEW || (o >= o0 && o < o1))
+      row[o] = *reinterpret_cast<const uint4*>(src + (size_t)(shift + jb * 16 + min(max(o, o0), o1 - 1)) * row_stride);
   if (blockIdx.z == 0) {
 #pragma unroll
     for (int o = 0; o < 16; ++o)
       if (o >= o0 && o < o1) *reinterpret_cast<uint4*>(kc + (size_t)o * a.D) = row[o];
-  } else if (o1 - o0 == 16) {
+  } else if (!FEW && o1 - o0 == 16) {
     uint4 out[16];  // this thread's 8 rows of the V tile, 256 contiguous bytes
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -127,12 +130,18 @@ hipError_t launch_kv_write(const aflex_kv_write_args& a, hipStream_t stream) {
   if (a.T == 0 || a.max_seqlen == 0) return hipSuccess;
   const int slots = (a.max_seqlen + 15) / 16 + 1;
   ProfScope ps("kv_write", stream);
-  // The exchange of V rows takes 256 bytes of LDS per thread: up to 64 KiB.
+  // The exchange of V rows takes 256 bytes of LDS per thread: up to 64 KiB. Wide
+  // rows of few tokens: 64 sequences of one token, 64 heads x 128, 10.8 us with
+  // only those rows loaded, 12.3 with 16; up to 256 threads no difference, and
+  // whole blocks are 3-20% slower with the condition.
   const int threads = a.Hkv * (a.D / 8);
+  const dim3 grid(slots, a.B, 2);
   if (threads <= 256)
-    kv_write_kernel<true><<<dim3(slots, a.B, 2), threads, (threads + 15) / 16 * 4096, stream>>>(a);
+    kv_write_kernel<true, false><<<grid, threads, (threads + 15) / 16 * 4096, stream>>>(a);
+  else if (a.max_seqlen < 16)
+    kv_write_kernel<false, true><<<grid, threads, 0, stream>>>(a);
   else
-    kv_write_kernel<false><<<dim3(slots, a.B, 2), threads, 0, stream>>>(a);
+    kv_write_kernel<false, false><<<grid, threads, 0, stream>>>(a);
   return hipGetLastError();
 }
 
