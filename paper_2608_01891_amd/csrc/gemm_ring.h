@@ -133,10 +133,6 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
   } while (0)
 
   f32x4 acc[8][8];  // [row block][column block]
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // Byte offsets of this lane's fragments of k-chunk 0 and 1 in a half tile.
   const uint32_t off0 = r * 128 + ((qg ^ ((r >> 1) & 7)) << 4);
@@ -172,6 +168,18 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
         RING_ISSUE(Q, (decltype(s)::value * 4 + Q) * HB, L & 3);
       });
     });
+    // 256 accumulator registers of a wave, about a thousand cycles: behind the first
+    // loads (the empty statements keep the compiler from moving it past the wait).
+    // Before the loads and once more after the wait, k-loops of 8 and 16 steps
+    // took 3 and 5% longer (MoE 512 x 4096, T = 940 86.4 -> 89.3 us; linear 7168 x
+    // 9216, T = 256 59.4 -> 62.4).
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]), "+a"(acc[i][4]),
+                        "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7]));
+    }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(8 + N));
     __syncthreads();
     // Ring offsets: (u, v) of this k-step, vp = v of the one before (where the
@@ -227,23 +235,21 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmParams p) {
       asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]), "+a"(acc[i][4]),
                         "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7]));
   };
-  const int rows = x.row1 - x.row0;
-  if (nk > 0) {
-    if (rows > 224)
-      kloop(std::integral_constant<int, 8>{});
-    else if (rows > 192)
-      kloop(std::integral_constant<int, 7>{});
-    else if (rows > 160)
-      kloop(std::integral_constant<int, 6>{});
-    else if (rows > 128)
-      kloop(std::integral_constant<int, 5>{});
-    else if (rows > 96)
-      kloop(std::integral_constant<int, 4>{});
-    else if (rows > 64)
-      kloop(std::integral_constant<int, 3>{});
-    else
-      kloop(std::integral_constant<int, 2>{});
-  }
+  const int rows = x.row1 - x.row0;  // (no split is without a k-step)
+  if (rows > 224)
+    kloop(std::integral_constant<int, 8>{});
+  else if (rows > 192)
+    kloop(std::integral_constant<int, 7>{});
+  else if (rows > 160)
+    kloop(std::integral_constant<int, 6>{});
+  else if (rows > 128)
+    kloop(std::integral_constant<int, 5>{});
+  else if (rows > 96)
+    kloop(std::integral_constant<int, 4>{});
+  else if (rows > 64)
+    kloop(std::integral_constant<int, 3>{});
+  else
+    kloop(std::integral_constant<int, 2>{});
 #undef RING_ISSUE
 #undef RING_READ
 #undef RING_BOFF
