@@ -58,15 +58,33 @@ def test_qwen3_prefill_tokens_every_row_tile(gpu_lib, qwen3_weights):
     check_rows(y[rows], ref, what="qwen3 swiglu prefill T=4096 (every 256-row block)")
 
 
-@pytest.mark.parametrize("T", [32, 33, 64, 65, 100, 255, 257, 300, 406, 456, 511])
-def test_tile_plan_boundaries(gpu_lib, T):
-    """Token counts on both sides of the dense tile-size thresholds, and
-    partly filled last row tiles whose waves multiply 0 to 4 of their row
-    blocks (128-row tile with 100 rows; 256-row tails of 1, 44, 150, 200 and
-    255 rows)."""
-    x, w, _ = synth.custom_ffn(120 + T, T, 320, 640)
+def _check(T, H, I):
+    x, w, _ = synth.custom_ffn(120 + T, T, H, I)
     y = aflex.ffn_swiglu(x.to(DEV), w.to(DEV)).cpu()
-    check_rows(y, oracle.swiglu_ffn(x, w.w_gate, w.w_up, w.w_down), what=f"swiglu T={T}")
+    check_rows(y, oracle.swiglu_ffn(x, w.w_gate, w.w_up, w.w_down), what=f"swiglu {T}x{H}x{I}")
+
+
+@pytest.mark.parametrize("T", [32, 33, 64, 65, 100, 255, 257, 300, 406, 456, 511])
+def test_small_matrices(gpu_lib, T):
+    """32- and 64-row tiles, which matrices of a few column tiles take for all
+    these token counts: whole and partly filled last row tiles."""
+    _check(T, 320, 640)
+
+
+# (tokens, rows per tile) of a gate/up GEMM with more than 160 column tiles; the host test
+# of the plans pins the rows
+EDGE_H, EDGE_I = 64, 20608
+TILE_EDGES = [(32, 32), (33, 64), (64, 64), (65, 128), (100, 128), (128, 128), (129, 256), (255, 256), (257, 256),
+              (300, 256), (406, 256), (456, 256), (511, 256)]
+
+
+@pytest.mark.parametrize("T,rows", TILE_EDGES)
+def test_tile_plan_boundaries(gpu_lib, T, rows):
+    """Token counts on both sides of the dense tile-size thresholds, and
+    partly filled last row tiles whose waves multiply only some of their row
+    blocks (128-row tile with 65 and 100 rows; two 256-row tiles of 160 and 97 to
+    256 and 255 rows)."""
+    _check(T, EDGE_H, EDGE_I)
 
 
 @pytest.mark.parametrize("T,H,I", [(8, 128, 7168), (20, 128, 5120)])

@@ -118,7 +118,7 @@ def test_mixtral_shape_all_rows(gpu_lib, mixtral):
 
 def test_mixtral_2048_tokens_all_rows(gpu_lib, mixtral):
     """The MoE at 2048 tokens (seed 103), the MFMA-bound decode size timed by the
-    benchmark (256-row tiles, routing in three kernels): every row."""
+    benchmark (256-row tiles, routing in two kernels): every row."""
     T = 2048
     wl = synth.mixtral_moe(device=DEV, T=T, seed=103, weights=mixtral.ffn)
     y, r = aflex.moe_ffn(wl.x, wl.ffn, wl.router_logits, 2, routing=True)
@@ -150,7 +150,7 @@ def test_mixtral_prefill_tokens_every_row_tile(gpu_lib, mixtral):
 def test_routing_extremes(gpu_lib, T, E, k):
     """The largest supported expert count and top-k (E = 64, k = 8), top-1 over
     64 experts (many empty experts), and k = E; on both sides of the batch size
-    where routing moves from one work-group to one per 256 tokens (512), with
+    where routing moves from one work-group to one per 64 tokens (512), with
     ragged last chunks."""
     H, I = 128, 128
     x, w, logits = synth.custom_ffn(80 + E + k, T, H, I, E=E)
@@ -160,17 +160,34 @@ def test_routing_extremes(gpu_lib, T, E, k):
     check_rows(y.cpu(), ref, what=f"moe extremes T={T} E={E} k={k}")
 
 
-@pytest.mark.parametrize("T", [20, 160, 200, 384, 448, 576, 584, 600, 1024, 1200, 2048, 2500])
-def test_tile_shape_boundaries(gpu_lib, T):
-    """Average rows per expert on both sides of the tile-size thresholds with 8
-    experts and top-2: 32-row tiles (5), 64-row (40), 128-row with
-    non-temporal weights (50, 96), 128-row re-reading weights (112, 144),
-    256-row tiles (146, 150, 300, 625) and 320-row tiles (256, 512; experts
-    of either side of 320 and 640 rows)."""
-    x, w, logits = synth.custom_ffn(90 + T, T, 256, 192, E=8)
+def _check_moe(T, H, I):
+    x, w, logits = synth.custom_ffn(90 + T, T, H, I, E=8)
     y = aflex.moe_ffn(x.to(DEV), w.to(DEV), logits.to(DEV), 2).cpu()
     ref, _, _ = oracle.moe_ffn(x, logits, w.w_gate, w.w_up, w.w_down, 2)
-    check_rows(y, ref, what=f"moe tile boundary T={T}")
+    check_rows(y, ref, what=f"moe {T}x{H}x{I}")
+
+
+@pytest.mark.parametrize("T", [20, 160, 200, 384, 448, 576, 584, 600, 1024, 1200, 2048, 2500])
+def test_small_experts(gpu_lib, T):
+    """32-row tiles (T = 20) and 64-row ones, which experts of a few column tiles
+    take for any number of rows: one to ten row tiles per expert."""
+    _check_moe(T, 256, 192)
+
+
+# (tokens, rows per tile) of 8 experts, top-2, with 15 column tiles of 128; the host test
+# of the plans pins the rows
+EDGE_H, EDGE_I = 64, 1920
+TILE_EDGES = [(20, 32), (98, 32), (100, 64), (192, 64), (196, 128), (200, 128), (384, 128), (388, 256), (448, 256),
+              (600, 256), (1024, 256), (1200, 256), (2048, 320), (2100, 320), (2500, 256)]
+
+
+@pytest.mark.parametrize("T,rows", TILE_EDGES)
+def test_tile_shape_boundaries(gpu_lib, T, rows):
+    """Average rows per expert on both sides of the tile-size thresholds: 32-row
+    tiles (to 24), 64-row (25, 48), 128-row (49, 96), 256-row (97, 256, 300, 625) and
+    320-row ones that save a round of the chip (512, 525; experts of either side
+    of 320 rows)."""
+    _check_moe(T, EDGE_H, EDGE_I)
 
 
 @pytest.mark.parametrize("T,H,I,E,k", [(16, 128, 8192, 4, 3),     # 32-row tiles, 8 splits, k > 2

@@ -31,10 +31,15 @@ def _swiglu64(x, w):
     return (g / (1.0 + torch.exp(-g)) * u) @ w.w_down.double().t()
 
 
-# 168 MB of weights (past what is kept): 64-row tiles for few work-groups, else 128; 4 MB: 64-row tiles
-# up to 128 tokens and where larger ones are few
-@pytest.mark.parametrize("T", [1, 32, 33, 64, 65, 128, 129, 256, 257])
-@pytest.mark.parametrize("K,N", [(8192, 10304), (1024, 1984)])
+# Rows per tile of each call (the host test of the plans pins them): 168 MB of
+# weights, past what is kept, and 4 MB, few work-groups
+LINEAR_T = [1, 32, 33, 64, 65, 128, 129, 256, 257]
+LINEAR_ROWS = {(8192, 10304): [32, 32, 128, 128, 128, 128, 256, 256, 256],
+               (1024, 1984): [32, 32, 64, 64, 64, 64, 64, 64, 64]}
+
+
+@pytest.mark.parametrize("T", LINEAR_T)
+@pytest.mark.parametrize("K,N", LINEAR_ROWS)
 def test_linear(gpu_lib, T, K, N):
     x, w = _linear(K, N)
     x = x[:T]
@@ -45,17 +50,26 @@ def test_linear(gpu_lib, T, K, N):
 
 
 # first GEMMs of few (112, at 256 rows) and of enough work-groups; 176, 352 and 2 MB
-@pytest.mark.parametrize("T", [31, 33, 64, 100, 129, 256, 290])
-@pytest.mark.parametrize("H,I", [(2048, 14336), (2752, 21376), (576, 640)])
+SWIGLU_T = [31, 33, 64, 100, 129, 256, 290]
+SWIGLU_ROWS = {(2048, 14336): [32, 64, 64, 128, 128, 128, 256], (2752, 21376): [32, 128, 128, 128, 256, 256, 256],
+               (576, 640): [32, 64, 64, 64, 64, 64, 64]}
+
+
+@pytest.mark.parametrize("T", SWIGLU_T)
+@pytest.mark.parametrize("H,I", SWIGLU_ROWS)
 def test_swiglu(gpu_lib, T, H, I):
     x, w, _ = _ffn(H, I, 0)
     x = x[:T]
     check_rows(aflex.ffn_swiglu(x, w).cpu(), _swiglu64(x.double(), w).cpu(), what=f"swiglu {T}x{H}x{I}")
 
 
-# rows per expert: 32-, 64-, 128- and 256-row tiles, experts over and under one tile; 264 and 2 MB
-@pytest.mark.parametrize("T", [30, 80, 190, 200, 380, 500])
-@pytest.mark.parametrize("H,I", [(2048, 5376), (256, 320)])
+# experts over and under one tile; 264 and 2 MB
+MOE_T = [30, 80, 190, 200, 380, 500]
+MOE_ROWS = {(2048, 5376): [32, 64, 128, 256, 256, 256], (256, 320): [32, 64, 64, 64, 64, 64]}
+
+
+@pytest.mark.parametrize("T", MOE_T)
+@pytest.mark.parametrize("H,I", MOE_ROWS)
 def test_moe(gpu_lib, T, H, I):
     E, k = 4, 2
     x, w, logits = _ffn(H, I, E)

@@ -6,7 +6,7 @@ import subprocess
 import pytest
 
 from paper_2608_01891_amd import build
-from tests import test_gpu_tile_plan
+from tests import test_gpu_ffn, test_gpu_gemm_ring, test_gpu_moe, test_gpu_tile_plan
 
 MAIN = r"""
 #include <stdio.h>
@@ -102,3 +102,25 @@ def test_few_k_steps(plans, call, bm):
     + [(moe(*c), 320) for c in test_gpu_tile_plan.MOE_ONE_ROUND])
 def test_moe_one_round(plans, call, bm):
     assert plans([call])[0][0] == bm
+
+
+def test_the_ring_tests_take_256_row_tiles(plans):
+    r = test_gpu_gemm_ring
+    one = plans([linear(*c) for c in r.RING_LINEAR + r.RING_RESIDUAL])
+    assert [(p[0], p[2]) for p in one] == [(256, 1)] * len(one)
+    split = plans([linear(*c) for c in r.RING_LINEAR_SPLIT])
+    assert all(p[0] == 256 and p[2] > 1 for p in split)
+    assert {p[0] for p in plans([swiglu(*c) for c in r.RING_SWIGLU] + [moe(*c) for c in r.RING_MOE])} == {256}
+
+
+def test_the_boundary_tests_take_the_tiles_they_name(plans):
+    f, m, t = test_gpu_ffn, test_gpu_moe, test_gpu_tile_plan
+    assert [p[0] for p in plans([swiglu(T, f.EDGE_H, f.EDGE_I) for T, _ in f.TILE_EDGES])] == [b for _, b in f.TILE_EDGES]
+    assert [p[0] for p in plans([moe(T, m.EDGE_H, m.EDGE_I, 8, 2) for T, _ in m.TILE_EDGES])] == \
+        [b for _, b in m.TILE_EDGES]
+    for shape, rows in t.LINEAR_ROWS.items():
+        assert [p[0] for p in plans([linear(T, *shape) for T in t.LINEAR_T])] == rows, shape
+    for shape, rows in t.SWIGLU_ROWS.items():
+        assert [p[0] for p in plans([swiglu(T, *shape) for T in t.SWIGLU_T])] == rows, shape
+    for shape, rows in t.MOE_ROWS.items():
+        assert [p[0] for p in plans([moe(T, *shape, 4, 2) for T in t.MOE_T])] == rows, shape
