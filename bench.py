@@ -31,7 +31,7 @@ PEAK_BF16 = 2.5e15     # flop/s, dense bf16 MFMA
 METRIC = "attn-decode HBM GB/s & FFN bf16 TFLOPS vs peak; A/F layer-step tokens/s"
 DOMINANT = "gemm_gate_up"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gemm_gate_up_af_pipeline_traffic.json")
-KERNEL_SOURCES = ["gemm.h", "gemm_dispatch.hip", "ffn_plan.h", "moe.hip"]
+KERNEL_SOURCES = ["common.h", "gemm.h", "gemm_ring.h", "gemm_dispatch.hip", "ffn_plan.h", "moe.hip"]
 
 
 def _code_only(text):

@@ -2,6 +2,7 @@
 HBM-traffic counter readings, and the workload bookkeeping (no GPU)."""
 import json
 import os
+import re
 
 import bench
 
@@ -18,6 +19,19 @@ def test_kernel_hash_is_stable_and_covers_the_sources():
     assert h == bench.kernel_hash() and len(h) == 16
     for f in bench.KERNEL_SOURCES:
         assert os.path.exists(os.path.join(bench.ROOT, "paper_2608_01891_amd", "csrc", f)), f
+
+
+def test_kernel_hash_covers_what_the_gemms_include():
+    csrc = os.path.join(bench.ROOT, "paper_2608_01891_amd", "csrc")
+    todo, seen = ["gemm_dispatch.hip"], set()
+    while todo:
+        f = todo.pop()
+        if f in seen or f == "profile.h":  # (event timing around the launches)
+            continue
+        seen.add(f)
+        with open(os.path.join(csrc, f)) as fh:
+            todo += re.findall(r'#include "(\w+\.h)"', fh.read())
+    assert seen <= set(bench.KERNEL_SOURCES)
 
 
 def test_traffic_file_records_its_commands_and_calibration():
