@@ -28,14 +28,14 @@ struct FfnPlan {
 };
 
 // Rows per m-tile for grouped GEMMs with the given average rows per expert.
-// Up to 32 rows a tile covers a typical expert (its weights are streamed once,
-// non-temporally); up to 48 rows 64-row tiles, two work-groups per CU (an
-// expert's second tile re-reads its weights from L2; at 32 rows per expert
-// 535 us against 611 us with 128-row tiles); up to 96 rows the 8-wave 128-row
-// tile; beyond, the 256-row shape, which holds an expert of up to 256 rows in
-// one tile where more and more experts take two of 128 (Mixtral shapes, 80 rows
-// per expert: 510 us with 128-row tiles, 539 with 256; 95: 533 and 547; 112: 628
-// and 564; 127: 707 and 581; 144: 842 and 600).
+// Up to 32 rows a tile covers a typical expert (its weights are streamed once);
+// up to 48 rows 64-row tiles, two work-groups per CU, up to 96 rows the 8-wave
+// 128-row tile; beyond, the 256-row shape, which holds an expert of up to 256 rows
+// in one tile where more and more experts take two of 128. Mixtral shapes, 32
+// rows per expert: 481 us with 64-row tiles, 460 with 128; 47: 505 and 474; 60: 547
+// and 481 (for experts with few column tiles plan_moe goes back to 64); 80 rows: 508
+// us with 128-row tiles, 508 with 256; 95: 519 and 518; 112: 613 and 532; 127: 674
+// and 552; 144: 818 and 565.
 //
 // An expert's rows are split evenly over its row tiles (tile_rows below), so
 // one just over a multiple of 256 rows has no nearly empty tile that streams all
@@ -120,9 +120,11 @@ constexpr long long kKeepFewRowsBytes = 48ll << 20;
 constexpr int kFewWorkGroups = 160;
 // The same for MoE calls, whose tile count is an estimate (every expert the
 // average): so few that tiles of half the height still fit one round when the
-// estimate is off. E = 8, 512 x 512, k = 2, T = 1000: 55 -> 32 us with 64-row
-// tiles; E = 4, 1024 x 1024, T = 300: 56 -> 31; but with 144 work-groups (E = 3,
-// 4096 x 3008, T = 600) 128-row tiles 178, 256-row tiles 129 us.
+// estimate is off. E = 8, 512 x 512, k = 2, T = 1000: 54.7 us with 256-row tiles, 31.7
+// with 64; E = 4, 1024 x 1024, T = 300: 48.4 and 31.2; with 144 work-groups of 256
+// rows (E = 3, 4096 x 3008, k = 1, T = 1000) 127 us, with 128 rows 128. The line is not
+// tight: E = 2, 2048 x 4096, k = 1, T = 300, 128 work-groups of 128 rows, 64.7, with 64
+// rows 58.8.
 constexpr int kFewGroupedWorkGroups = 112;
 
 // Tiles of a MoE call. `once`: experts' rows are expected to fit one tile (average
@@ -163,8 +165,8 @@ inline MoePlan plan_moe(long long pairs, int H, int I, int E, int k) {
   if (pl.bm == 256) {
     const int ntiles = (I + gate_bn(256) - 1) / gate_bn(256), round = concurrent_wgs(256);
     const double sigma = sqrt(rows * (1.0 - (double)k / E));  // tokens choose independently
-    if (floor(expected_tiles256(E, rows, sigma) + 0.5) * ntiles > round &&
-        E * ceil((rows + 3.0 * sigma) / 320.0) * ntiles <= round)
+    if (E * ceil((rows + 3.0 * sigma) / 320.0) * ntiles <= round &&
+        floor(expected_tiles256(E, rows, sigma) + 0.5) * ntiles > round)
       pl.bm = 320;
   }
   pl.once = pl.bm == 32 || (pl.bm != 320 && rows * 1.3 <= (double)pl.bm);
