@@ -214,6 +214,11 @@ def _stream(s):
     return s.cuda_stream
 
 
+def _need_gpu(device):
+    if torch.device(device).type != "cuda":
+        raise ValueError(f"expected tensors on a cuda device, but got: {device}")
+
+
 class Workspace:
     """Grow-only device scratch handed to the library (allocated by torch)."""
 
@@ -226,6 +231,7 @@ class Workspace:
 
     def get(self, nbytes: int, device):
         if not self.fits(nbytes, device):
+            _need_gpu(device)
             self.buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
         return self.buf
 
@@ -254,10 +260,9 @@ def _run(name, args, key, device, ws, stream):
     queried. (Two library calls, a Stream object and keyword-built argument
     blocks per call held a tiny layer's attention, 5 us on the GPU, at 11.3 us.)
 
-    Tensors that are not on a GPU are refused here, before any library call: a
-    kernel would read and write the host's addresses."""
-    if device.type != "cuda":
-        raise ValueError(f"{name}: expected tensors on a cuda device, but got: {device}")
+    Tensors that are not on a GPU are refused before any library call (a kernel would
+    read and write the host's addresses): no workspace is ever on another device, so
+    theirs is never at hand."""
     if ws is None:
         ws = _default_ws.get(key)
         if ws is None:
@@ -270,6 +275,7 @@ def _run(name, args, key, device, ws, stream):
         if status != ERR_WORKSPACE:
             _check(status)
             return
+    _need_gpu(device)
     n = ctypes.c_size_t()
     _check(getattr(_lib, name + "_workspace")(ref, ctypes.byref(n)))
     p, sz = _ws(key, n.value, device, ws, (stream,))

@@ -275,3 +275,5 @@ def test_host_tensors_are_refused_before_any_library_call(lib, monkeypatch, op, 
     with pytest.raises(ValueError, match="cuda device"):
         call()
     assert calls == []
+    with pytest.raises(ValueError, match="cuda device"):  # nor is a workspace made that would fit them
+        (ws or aflex.Workspace()).get(256, "cpu")
