@@ -20,8 +20,9 @@
 // are loaded and multiplied (in instances of 2 to 8 blocks per wave).
 //
 // Measured (dense SwiGLU, H = 5120, I = 25600; the eight-wave 32x32x16 tiles
-// with two 64-wide stages before): T = 4096 2870 -> 2350 us (1.12 -> 1.37
-// PFLOP/s), T = 512 427 -> 355 us; 8192^3 linear 895 -> 720 us. Bit-identical.
+// with two 64-wide stages before, both on one GPU): T = 4096 2854 -> 2384 us
+// (1.13 -> 1.35 PFLOP/s), T = 512 423 -> 358 us; 8192^3 linear 885 -> 740 us.
+// Bit-identical. (k-loops of few steps gain less or lose: kFewSteps in ffn_plan.h.)
 // Tried and slower: a barrier after each quarter of the tile that frees half
 // tiles earlier (eight waves; 13% less), two barriers per k-step (1-2%),
 // persistent work-groups that load the next tile's first k-steps under the
