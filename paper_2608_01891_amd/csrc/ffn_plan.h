@@ -192,6 +192,15 @@ constexpr long long kSmallTileBytes = 84ll << 20;
 // T = 1536, 2 splits and 1 45.2 and 65.9).
 constexpr int kFewSteps = 16;
 
+// k-steps per split up to which a linear layer's 256-row tiles do not take several
+// rounds of work-groups, however full, but the splits that one round holds: every
+// split adds [T, N] of fp32 partials, written and read, and a k-loop's beginning
+// and end. 6144 x 3072, T = 1400, 72 tiles: 7 splits 91 us, 5 90, 3 (one round, 84%
+// full) 61; T = 3000, 144 tiles: 5 splits of 20 steps 168, one 111; 3072 x 6144, T =
+// 1400, 144 tiles: 5 splits of 10 steps 109, one 62; 7168 x 9216, T = 448, 72 tiles: 7
+// splits of 16 88, 3 67.
+constexpr int kFewStepsOfRounds = 24;
+
 // Plan of a linear layer [N, K] (gate_cols = 0) or of a SwiGLU whose down matrix
 // is [N, K] and whose gate and up matrices are [gate_cols, N]: the largest tile
 // of 256, 128 or 64 rows whose first GEMM has enough work-groups, unless the next
@@ -200,9 +209,10 @@ constexpr int kFewSteps = 16;
 // 20.5 -> 11.3.
 //
 // Up to 64 tokens, where one 64-row tile holds all rows, weights that stay cached
-// take it, unless a linear layer's work-groups are a few more than the CUs, some
-// of which then hold two (4096 x 5120, T = 40, 320 work-groups of 64 rows or 160
-// of 128: 18.0 and 17.3 us; 4096 x 4096, 256 or 128: 13.5 and 16.4). From 65 on
+// take it. Where a linear layer's work-groups would be a few more than the CUs,
+// some of which then hold two, it takes the splits that give each CU one at most
+// (4096 x 5120, T = 40: 320 work-groups 18.0 us, 240 14.7, 160 of 128 rows 17.3; 2560 x
+// 8192: 320 19.6, 256 15.0). From 65 on
 // two 64-row tiles read every weight twice, which pays only where the 128-row
 // tiles leave CUs idle (SwiGLU 2048 x 8192, T = 128, 64 work-groups of 128 rows:
 // 43.0 us with 64-row tiles, 57.1 with 128; 1024 x 25600, 200 work-groups: 68.0
@@ -219,6 +229,10 @@ inline FfnPlan plan_dense(int T, int N, int K, int gate_cols) {
     pl.bm = bm;
     plan_splits(mtiles * ntiles, K, down_target(bm), concurrent_wgs(bm), 8, &pl.down_splits, &pl.down_kps);
     return (long long)mtiles * (gate_cols ? (gate_cols + gate_bn(bm) - 1) / gate_bn(bm) : ntiles * pl.down_splits);
+  };
+  auto at_most = [&](int wgs) {  // the splits of pl.bm that give at most this many work-groups, one at least
+    const int tiles = (T + pl.bm - 1) / pl.bm * ((N + down_bn(pl.bm) - 1) / down_bn(pl.bm));
+    plan_splits(tiles, K, wgs / tiles * tiles, 0, 8, &pl.down_splits, &pl.down_kps);
   };
   auto one_round = [&](int bm, long long n) {  // of resident work-groups, nearly full
     return n <= concurrent_wgs(bm) && n * 16 >= concurrent_wgs(bm) * 15ll;
@@ -237,17 +251,20 @@ inline FfnPlan plan_dense(int T, int N, int K, int gate_cols) {
       const long long n128 = try_bm(128);
       if (!one_round(128, n128) && (n128 < n256 || n128 > concurrent_wgs(128) || pl.down_splits == 1)) try_bm(256);
     }
+    if (!gate_cols && pl.bm == 256 && n256 > concurrent_wgs(256) && pl.down_kps <= kFewStepsOfRounds * 64)
+      at_most(concurrent_wgs(256));
   } else {
-    const long long n64 = try_bm(64), n128 = try_bm(128);
+    const long long n64 = try_bm(64), tiles64 = n64 / (gate_cols ? 1 : pl.down_splits), n128 = try_bm(128);
     const bool few = n128 <= kFewWorkGroups;
     bool small;
-    if (T <= 64 && gate_cols)
-      small = few || keep;
-    else if (T <= 64)
-      small = n64 <= 256 || (n64 >= 384 && bytes <= kSmallTileBytes);
+    if (T <= 64)
+      small = gate_cols ? few || keep : n64 <= 256 || (bytes <= kSmallTileBytes && (tiles64 <= 256 || n64 >= 384));
     else
       small = keep && (few || (!gate_cols && bytes <= kSmallTileBytes && (one_round(64, n64) || !one_round(128, n128))));
-    if (small) try_bm(64);
+    if (small) {
+      try_bm(64);
+      if (T <= 64 && !gate_cols && n64 > 256 && n64 < 384) at_most(256);
+    }
   }
   pl.nt = !keep && T <= pl.bm;
   return pl;

@@ -21,7 +21,7 @@ RING_LINEAR = [(129, 64, 41024), (160, 128, 41088), (161, 192, 41152), (193, 64,
                (257, 320, 23040), (300, 64, 25600), (2120, 128, 4672), (2305, 64, 4160), (2305, 192, 4352),
                (2305, 320, 5120), (513, 448, 13888), (385, 960, 20544)]
 # ... and with several (fp32 partials)
-RING_LINEAR_SPLIT = [(2305, 2048, 4352), (300, 8192, 5376), (256, 7168, 9216), (257, 8192, 5120)]
+RING_LINEAR_SPLIT = [(2305, 4096, 2560), (1400, 6144, 3072), (300, 8192, 5376), (256, 7168, 9216), (257, 8192, 5120)]
 
 
 def _linear(T, K, N):

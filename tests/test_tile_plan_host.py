@@ -75,7 +75,7 @@ def test_non_temporal_weights(plans, call, nt):
     (linear(33, 8192, 5120), 64), (linear(64, 8192, 5120), 64), (linear(128, 8192, 5120), 64),
     (linear(64, 5120, 10240), 128), (linear(96, 7168, 9216), 128), (linear(128, 4096, 11264), 128),
     (linear(80, 4096, 9216), 128),
-    (linear(40, 4096, 5120), 128), (linear(72, 4096, 5120), 64), (linear(40, 4096, 4096), 64), (linear(40, 5120, 5120), 64), (linear(128, 2048, 16384), 64), (linear(128, 2048, 1024), 64),
+    (linear(40, 4096, 5120), 64), (linear(72, 4096, 5120), 64), (linear(40, 4096, 4096), 64), (linear(40, 5120, 5120), 64), (linear(128, 2048, 16384), 64), (linear(128, 2048, 1024), 64),
     (linear(64, 8192, 10304), 128), (linear(128, 8192, 10304), 128),
     (swiglu(64, 1024, 25600), 64), (swiglu(65, 1024, 25600), 128), (swiglu(128, 2048, 8192), 64),
     (swiglu(64, 4096, 14336), 64), (swiglu(65, 4096, 14336), 128), (swiglu(33, 5120, 25600), 128)])
@@ -124,3 +124,12 @@ def test_the_boundary_tests_take_the_tiles_they_name(plans):
         assert [p[0] for p in plans([swiglu(T, *shape) for T in t.SWIGLU_T])] == rows, shape
     for shape, rows in t.MOE_ROWS.items():
         assert [p[0] for p in plans([moe(T, *shape, 4, 2) for T in t.MOE_T])] == rows, shape
+
+
+# splits of linear layers: one work-group per CU instead of a few more, one round instead of several short ones
+@pytest.mark.parametrize("call,splits", [
+    (linear(40, 4096, 5120), 6), (linear(64, 2560, 8192), 4), (linear(40, 4096, 4096), 8), (linear(64, 8192, 5120), 12),
+    (linear(40, 1024, 36864), 1), (linear(1400, 3072, 6144), 1), (linear(1400, 6144, 3072), 3), (linear(3000, 6144, 3072), 1),
+    (linear(3000, 3072, 6144), 1), (linear(448, 7168, 9216), 3), (linear(256, 7168, 9216), 7), (linear(2048, 5120, 5120), 3)])
+def test_linear_splits(plans, call, splits):
+    assert plans([call])[0][2] == splits
